@@ -4,10 +4,7 @@
 // grouped by cluster. Every decision is exact, so the result equals the CPU
 // definition bit for bit:
 //   * assignment: argmax over centroids of the fp64 score S64 (dimension order),
-//     lowest id among equal scores. The fp32 matrix-core filter scores f satisfy
-//     |f - S64| <= kFilterEps for tokens and centroids of norm <= 1 + 1e-3, so the
-//     argmax is among the centroids with f >= max f - 2 kFilterEps; those are
-//     rescored in fp64;
+//     lowest id among equal scores (assign.hip);
 //   * k-means update: the sum over assigned sample tokens of round(x * 2^30) per
 //     dimension (exact int64), normalised in fp64 (dimension-order sum of
 //     squares, IEEE sqrt and division) and rounded to fp32; a centroid without
@@ -25,86 +22,6 @@
 #include "engine.h"
 
 namespace warp {
-
-constexpr int kArgBlock = 256;
-constexpr int kArgCap = 1024;  // candidates within the filter band of one token
-
-__device__ __forceinline__ double dot64(const float* __restrict__ c, const float* __restrict__ x) {
-    double s = 0.0;
-    for (int d = 0; d < kDim; ++d) s += (double)c[d] * (double)x[d];
-    return s;
-}
-
-// assign[t] for tokens [t0, t0 + n) from their fp32 filter scores [n][n_c]
-__global__ __launch_bounds__(kArgBlock) void k_rows_argmax(const float* __restrict__ scores, int32_t n_c,
-                                                           const float* __restrict__ x, const float* __restrict__ cen,
-                                                           int32_t* __restrict__ assign, int32_t* err) {
-    __shared__ float s_max[kArgBlock / 64];
-    __shared__ int s_n;
-    __shared__ int s_id[kArgCap];
-    __shared__ double s_best[kArgBlock / 64];
-    __shared__ int s_bid[kArgBlock / 64];
-    const int64_t t = blockIdx.x;
-    const int tid = threadIdx.x;
-    const float* row = scores + t * n_c;
-    float m = -INFINITY;
-    for (int c = tid; c < n_c; c += kArgBlock) m = fmaxf(m, row[c]);
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if ((tid & 63) == 0) s_max[tid >> 6] = m;
-    if (tid == 0) s_n = 0;
-    __syncthreads();
-    float mx = s_max[0];
-    for (int w = 1; w < kArgBlock / 64; ++w) mx = fmaxf(mx, s_max[w]);
-    const float thr = mx - 2.5f * kFilterEps;
-    for (int c = tid; c < n_c; c += kArgBlock)
-        if (row[c] >= thr) {
-            const int p = atomicAdd(&s_n, 1);
-            if (p < kArgCap) s_id[p] = c;
-        }
-    __syncthreads();
-    const int n = s_n;
-    if (n > kArgCap) {
-        if (tid == 0) {
-            atomicOr(err, kErrArgOverflow);
-            assign[t] = 0;
-        }
-        return;
-    }
-    const float* xt = x + t * kDim;
-    double best = -INFINITY;
-    int bid = INT32_MAX;
-    for (int p = tid; p < n; p += kArgBlock) {
-        const int c = s_id[p];
-        const double s = dot64(cen + (int64_t)c * kDim, xt);
-        if (s > best || (s == best && c < bid)) {
-            best = s;
-            bid = c;
-        }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        const double ob = __shfl_xor(best, off, 64);
-        const int oi = __shfl_xor(bid, off, 64);
-        if (ob > best || (ob == best && oi < bid)) {
-            best = ob;
-            bid = oi;
-        }
-    }
-    if ((tid & 63) == 0) {
-        s_best[tid >> 6] = best;
-        s_bid[tid >> 6] = bid;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        best = s_best[0];
-        bid = s_bid[0];
-        for (int w = 1; w < kArgBlock / 64; ++w)
-            if (s_best[w] > best || (s_best[w] == best && s_bid[w] < bid)) {
-                best = s_best[w];
-                bid = s_bid[w];
-            }
-        assign[t] = bid;
-    }
-}
 
 __global__ void k_gather_rows(const float* __restrict__ x, const int64_t* __restrict__ ids, int64_t n,
                               float* __restrict__ out) {
@@ -176,37 +93,81 @@ __global__ void k_pick_quantiles(const float* __restrict__ sorted, int64_t n, in
     if (j < nb) weights[j] = at(2 * j + 1, nbits + 1);
 }
 
-// embeddings in cluster order: codes and document ids at position p of token perm[p]
+// embeddings in cluster order: codes and document ids at position p of token perm[p]. A thread
+// makes four code bytes (32 / NBITS dimensions) from 16-byte loads; the cutoffs stand in LDS.
 template <int NBITS>
-__global__ void k_encode(const float* __restrict__ x, const int32_t* __restrict__ token_docs,
-                         const int32_t* __restrict__ assign, const int64_t* __restrict__ perm, int64_t n,
-                         const float* __restrict__ cen, const float* __restrict__ cutoffs,
-                         uint8_t* __restrict__ codes, int32_t* __restrict__ doc_ids) {
+__global__ __launch_bounds__(256) void k_encode(const float* __restrict__ x, const int32_t* __restrict__ token_docs,
+                                                const int32_t* __restrict__ assign, const int64_t* __restrict__ perm,
+                                                int64_t n, const float* __restrict__ cen,
+                                                const float* __restrict__ cutoffs, uint32_t* __restrict__ codes,
+                                                int32_t* __restrict__ doc_ids) {
     constexpr int NB = 1 << NBITS;
-    constexpr int PER = 8 / NBITS;  // dimensions per byte
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (position, byte)
-    constexpr int BYTES = kDim * NBITS / 8;
-    if (i >= n * BYTES) return;
-    const int64_t p = i / BYTES;
-    const int byte = (int)(i % BYTES);
+    constexpr int WORDS = kDim * NBITS / 32;  // code words per embedding
+    constexpr int DIMS = 32 / NBITS;          // dimensions per word
+    __shared__ float s_cut[NB];
+    if (threadIdx.x < NB - 1) s_cut[threadIdx.x] = cutoffs[threadIdx.x];
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (position, word)
+    if (i >= n * WORDS) return;
+    const int64_t p = i / WORDS;
+    const int word = (int)(i % WORDS);
     const int64_t t = perm[p];
     const int c = assign[t];
+    const float4* xr = reinterpret_cast<const float4*>(x + t * kDim + word * DIMS);
+    const float4* cr = reinterpret_cast<const float4*>(cen + (int64_t)c * kDim + word * DIMS);
     unsigned v = 0;
-    for (int u = 0; u < PER; ++u) {
-        const int d = byte * PER + u;
-        const float r = x[t * kDim + d] - cen[(int64_t)c * kDim + d];
-        int code = 0;  // number of cutoffs <= r (cutoffs ascend)
-        int lo = 0, hi = NB - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (cutoffs[mid] <= r) lo = mid + 1;
-            else hi = mid;
+#pragma unroll
+    for (int k = 0; k < DIMS / 4; ++k) {
+        const float4 a = xr[k], b = cr[k];
+        const float r[4] = {a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int d = 4 * k + u;
+            int lo = 0, hi = NB - 1;  // the number of cutoffs <= r (cutoffs ascend)
+#pragma unroll
+            for (int step = 0; step < NBITS; ++step) {
+                const int mid = (lo + hi) >> 1;
+                if (s_cut[mid] <= r[u]) lo = mid + 1;
+                else hi = mid;
+            }
+            // the word's bytes in memory order, the first dimension of a byte in its top bits
+            const int byte = d * NBITS / 8;
+            v |= (unsigned)lo << (8 * byte + 8 - NBITS * (d % (8 / NBITS) + 1));
         }
-        code = lo;
-        v |= (unsigned)code << (8 - NBITS * (u + 1));
     }
-    codes[p * BYTES + byte] = (uint8_t)v;
-    if (byte == 0) doc_ids[p] = token_docs[t];
+    if (((uintptr_t)codes & 3) == 0) {  // uniform
+        codes[i] = v;
+    } else {
+        uint8_t* b = reinterpret_cast<uint8_t*>(codes) + 4 * i;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) b[k] = (uint8_t)(v >> (8 * k));
+    }
+    if (word == 0) doc_ids[p] = token_docs[t];
+}
+
+// First starting vector that is not finite or whose squared norm is zero or not finite, one
+// thread each: *first becomes the smallest 2 c + (finite).
+__global__ void k_check_start(const float* __restrict__ rows, int32_t n, unsigned long long* first) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    const float4* r = reinterpret_cast<const float4*>(rows + (int64_t)c * kDim);
+    double ss = 0.0;
+    bool finite = true;
+    for (int d = 0; d < kDim / 4; ++d) {
+        const float4 v = r[d];
+        finite &= __builtin_isfinite(v.x) && __builtin_isfinite(v.y) && __builtin_isfinite(v.z) && __builtin_isfinite(v.w);
+        ss += (double)v.x * v.x;
+        ss += (double)v.y * v.y;
+        ss += (double)v.z * v.z;
+        ss += (double)v.w * v.w;
+    }
+    if (!finite || !(ss > 0.0) || !__builtin_isfinite(ss)) atomicMin(first, 2ull * (unsigned)c + (finite ? 1 : 0));
+}
+
+// First sample id outside [0, n_tokens).
+__global__ void k_check_sample(const int64_t* __restrict__ ids, int64_t n, int64_t n_tokens, unsigned long long* first) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n && (ids[i] < 0 || ids[i] >= n_tokens)) atomicMin(first, (unsigned long long)i);
 }
 
 __global__ void k_count_clusters(const int32_t* __restrict__ assign, int64_t n, unsigned long long* counts) {
@@ -222,11 +183,6 @@ __global__ void k_iota64(int64_t* out, int64_t n) {
 // ---------------------------------------------------------------------------- launchers
 
 static unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
-
-void launch_rows_argmax(const float* scores, int64_t n, int32_t n_c, const float* x, const float* cen,
-                        int32_t* assign, int32_t* err, hipStream_t s) {
-    if (n > 0) hipLaunchKernelGGL(k_rows_argmax, dim3((unsigned)n), dim3(kArgBlock), 0, s, scores, n_c, x, cen, assign, err);
-}
 
 void launch_gather_rows(const float* x, const int64_t* ids, int64_t n, float* out, hipStream_t s) {
     if (n > 0) hipLaunchKernelGGL(k_gather_rows, dim3(blocks_for(n * kDim, 256)), dim3(256), 0, s, x, ids, n, out);
@@ -261,15 +217,22 @@ void launch_pick_quantiles(const float* sorted, int64_t n, int32_t nbits, float*
 void launch_encode(int32_t nbits, const float* x, const int32_t* token_docs, const int32_t* assign,
                    const int64_t* perm, int64_t n, const float* cen, const float* cutoffs, uint8_t* codes,
                    int32_t* doc_ids, hipStream_t s) {
-    const int64_t work = n * (kDim * nbits / 8);
+    const int64_t work = n * (kDim * nbits / 32);
     if (work <= 0) return;
+    uint32_t* words = reinterpret_cast<uint32_t*>(codes);
     const dim3 grid(blocks_for(work, 256)), block(256);
     switch (nbits) {
-        case 1: hipLaunchKernelGGL(k_encode<1>, grid, block, 0, s, x, token_docs, assign, perm, n, cen, cutoffs, codes, doc_ids); break;
-        case 2: hipLaunchKernelGGL(k_encode<2>, grid, block, 0, s, x, token_docs, assign, perm, n, cen, cutoffs, codes, doc_ids); break;
-        case 4: hipLaunchKernelGGL(k_encode<4>, grid, block, 0, s, x, token_docs, assign, perm, n, cen, cutoffs, codes, doc_ids); break;
-        default: hipLaunchKernelGGL(k_encode<8>, grid, block, 0, s, x, token_docs, assign, perm, n, cen, cutoffs, codes, doc_ids); break;
+        case 1: hipLaunchKernelGGL(k_encode<1>, grid, block, 0, s, x, token_docs, assign, perm, n, cen, cutoffs, words, doc_ids); break;
+        case 2: hipLaunchKernelGGL(k_encode<2>, grid, block, 0, s, x, token_docs, assign, perm, n, cen, cutoffs, words, doc_ids); break;
+        case 4: hipLaunchKernelGGL(k_encode<4>, grid, block, 0, s, x, token_docs, assign, perm, n, cen, cutoffs, words, doc_ids); break;
+        default: hipLaunchKernelGGL(k_encode<8>, grid, block, 0, s, x, token_docs, assign, perm, n, cen, cutoffs, words, doc_ids); break;
     }
+}
+
+void launch_check_build(const float* rows, int32_t n_c, const int64_t* ids, int64_t n, int64_t n_tokens,
+                        unsigned long long* first, hipStream_t s) {
+    hipLaunchKernelGGL(k_check_start, dim3(blocks_for(n_c, 64)), dim3(64), 0, s, rows, n_c, first);
+    hipLaunchKernelGGL(k_check_sample, dim3(blocks_for(n, 256)), dim3(256), 0, s, ids, n, n_tokens, first + 1);
 }
 
 void launch_count_clusters(const int32_t* assign, int64_t n, unsigned long long* counts, hipStream_t s) {

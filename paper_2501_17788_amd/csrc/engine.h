@@ -180,9 +180,10 @@ void launch_check_queries(const float* q, int64_t n_tok, int32_t* err, hipStream
 void launch_doc_len(const int32_t* doc_ids, int64_t n, int32_t* doc_len, int32_t n_docs, hipStream_t s);
 
 // index construction
-constexpr int kErrArgOverflow = 1 << 10;  // more than kArgCap centroids in one token's argmax band
-void launch_rows_argmax(const float* scores, int64_t n, int32_t n_c, const float* x, const float* cen,
-                        int32_t* assign, int32_t* err, hipStream_t s);
+constexpr int kErrArgOverflow = 1 << 10;  // more than 1,024 centroids in one token's argmax band
+size_t assign_scratch_bytes(int64_t n, int32_t n_c);
+void launch_assign(const float* x, int64_t n, const float* cen, int32_t n_c, void* scratch, int32_t* out, int32_t* err,
+                   hipStream_t s);
 void launch_gather_rows(const float* x, const int64_t* ids, int64_t n, float* out, hipStream_t s);
 void launch_kmeans_accum(const float* xs, const int32_t* assign, int64_t n, unsigned long long* sums,
                          unsigned long long* counts, hipStream_t s);
@@ -196,6 +197,10 @@ void launch_pick_quantiles(const float* sorted, int64_t n, int32_t nbits, float*
 void launch_encode(int32_t nbits, const float* x, const int32_t* token_docs, const int32_t* assign,
                    const int64_t* perm, int64_t n, const float* cen, const float* cutoffs, uint8_t* codes,
                    int32_t* doc_ids, hipStream_t s);
+// first[0]: the smallest 2 c + (whether it is finite) of an unusable starting vector c; first[1]: the
+// first sample id out of range (both untouched where there is none)
+void launch_check_build(const float* rows, int32_t n_c, const int64_t* ids, int64_t n, int64_t n_tokens,
+                        unsigned long long* first, hipStream_t s);
 void launch_count_clusters(const int32_t* assign, int64_t n, unsigned long long* counts, hipStream_t s);
 void launch_iota64(int64_t* out, int64_t n, hipStream_t s);
 hipError_t sort_floats(void* temp, size_t* temp_bytes, const float* in, float* out, int64_t n, hipStream_t s);

@@ -1159,119 +1159,132 @@ int warp_build_index(const float* tokens, const int32_t* token_docs, int64_t n_t
     int rc = check_device();
     if (rc) return rc;
     const int64_t n_c = n_centroids;
-    // host checks of the small inputs
-    std::vector<float> hC((size_t)n_c * kDim);
-    std::vector<int64_t> hS((size_t)n_sample);
-    HIP_TRY(hipMemcpy(hC.data(), init_centroids, hC.size() * 4, hipMemcpyDefault));
-    HIP_TRY(hipMemcpy(hS.data(), sample_ids, hS.size() * 8, hipMemcpyDefault));
-    for (int64_t c = 0; c < n_c; ++c) {
-        double ss = 0;
-        for (int d = 0; d < kDim; ++d) {
-            const float v = hC[(size_t)c * kDim + d];
-            if (!std::isfinite(v)) return fail(WARP_EINVAL, "starting vector %lld is not finite", (long long)c);
-            ss += (double)v * v;
-        }
-        if (!(ss > 0.0) || !std::isfinite(ss))
-            return fail(WARP_EINVAL, "starting vector %lld is zero or too large", (long long)c);
-    }
-    for (int64_t i = 0; i < n_sample; ++i)
-        if (hS[i] < 0 || hS[i] >= n_tokens) return fail(WARP_EINVAL, "sample id %lld is out of range", (long long)i);
-
     hipStream_t s = nullptr;
     HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-    struct Scratch {
-        DevBuf err, assign, scores, xs, assign_s, sums, counts, resid, sorted, temp, perm_in, perm, keys;
-        ~Scratch() {
-            for (DevBuf* b : {&err, &assign, &scores, &xs, &assign_s, &sums, &counts, &resid, &sorted, &temp,
-                              &perm_in, &perm, &keys})
-                release(*b);
-        }
-    } w;
+    const int64_t N = n_tokens;
+    int end_bit = 1;
+    while (end_bit < 31 && ((int64_t)1 << end_bit) < n_c) ++end_bit;
+    size_t tb = 0, t1 = 0, t2 = 0, t3 = 0;
+    DevBuf mem;  // all scratch, in one allocation
     auto done = [&](int code) {
         (void)hipStreamSynchronize(s);
         (void)hipStreamDestroy(s);
+        release(mem);
         return code;
     };
-    const int64_t N = n_tokens;
-    const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(N, ((int64_t)1 << 31) / (n_c * 4)));
-    size_t tb = 0, t1 = 0, t2 = 0, t3 = 0;
-    if (!rc) rc = grow(w.err, 4);
-    if (!rc && !assignment) rc = grow(w.assign, (size_t)N * 4);
-    if (!rc) rc = grow(w.scores, (size_t)chunk * n_c * 4);
-    if (!rc) rc = grow(w.xs, (size_t)n_sample * kDim * 4);
-    if (!rc) rc = grow(w.assign_s, (size_t)n_sample * 4);
-    if (!rc) rc = grow(w.sums, (size_t)n_c * kDim * 8);
-    if (!rc) rc = grow(w.counts, ((size_t)n_c + 1) * 8);
-    if (!rc) rc = grow(w.resid, (size_t)n_quant * kDim * 4);
-    if (!rc) rc = grow(w.sorted, (size_t)n_quant * kDim * 4);
-    if (!rc) rc = grow(w.perm_in, (size_t)N * 8);
-    if (!rc) rc = grow(w.perm, (size_t)N * 8);
-    if (!rc) rc = grow(w.keys, (size_t)N * 4);
-    if (rc) return done(rc);
-    int end_bit = 1;
-    while (end_bit < 31 && ((int64_t)1 << end_bit) < n_c) ++end_bit;
     if (sort_floats(nullptr, &t1, nullptr, nullptr, n_quant * kDim, s) != hipSuccess ||
         sort_by_cluster(nullptr, &t2, nullptr, nullptr, nullptr, nullptr, N, end_bit, s) != hipSuccess ||
         exclusive_sum_u64(nullptr, &t3, nullptr, nullptr, n_c + 1, s) != hipSuccess)
         return done(fail(WARP_EDEVICE, "device primitive sizing failed"));
-    tb = std::max(t1, std::max(t2, t3));
-    rc = grow(w.temp, tb);
-    if (rc) return done(rc);
-    int32_t* err = (int32_t*)w.err.p;
-    int32_t* assign = assignment ? assignment : (int32_t*)w.assign.p;
+    struct {
+        int32_t *err, *assign, *assign_s, *keys;
+        unsigned long long *first, *sums, *counts;
+        void *match, *temp;
+        float *xs, *resid, *sorted;
+        int64_t *perm_in, *perm;
+    } w{};
+    const size_t temp_bytes = std::max(t1, std::max(t2, t3));
+    size_t total = 0;
+    for (int pass = 0; pass < 2; ++pass) {  // sizes, then the pieces
+        size_t at = 0;
+        auto take = [&](auto** p, size_t bytes) {
+            if (mem.p) *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>((char*)mem.p + at);
+            at += (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255;
+        };
+        take(&w.err, 4);
+        take(&w.first, 16);
+        take(&w.assign, assignment ? 0 : (size_t)N * 4);
+        take((char**)&w.match,
+             std::max(assign_scratch_bytes(N, n_centroids), assign_scratch_bytes(n_sample, n_centroids)));
+        take(&w.xs, (size_t)n_sample * kDim * 4);
+        take(&w.assign_s, (size_t)n_sample * 4);
+        take(&w.sums, (size_t)n_c * kDim * 8);
+        take(&w.counts, ((size_t)n_c + 1) * 8);
+        take(&w.resid, (size_t)n_quant * kDim * 4);
+        take(&w.sorted, (size_t)n_quant * kDim * 4);
+        take(&w.perm_in, (size_t)N * 8);
+        take(&w.perm, (size_t)N * 8);
+        take(&w.keys, (size_t)N * 4);
+        take((char**)&w.temp, temp_bytes);
+        total = at;
+        if (pass == 0) {
+            rc = grow(mem, total);
+            if (rc) return done(rc);
+        }
+    }
+    int32_t* err = w.err;
+    int32_t* assign = assignment ? assignment : w.assign;
 
-    // inputs: finite tokens of norm <= 1 + 1e-3, document ids in range
+    // inputs: usable starting vectors, sample ids in range, finite tokens of norm <= 1 + 1e-3,
+    // document ids in range; the starting centroids are normalised where they will stay
+    auto try_hip = [&](hipError_t e, const char* what) {
+        return e == hipSuccess ? WARP_OK : fail(WARP_EDEVICE, "%s failed: %s", what, hipGetErrorString(e));
+    };
     launch_fill_i32(err, 1, 0, s);
+    launch_fill_i32((int32_t*)w.first, 4, -1, s);
+    // (by way of the scratch: the two arrays may overlap)
+    rc = try_hip(hipMemcpyAsync(w.sums, init_centroids, (size_t)n_c * kDim * 4, hipMemcpyDefault, s),
+                 "copying the starting vectors");
+    if (!rc)
+        rc = try_hip(hipMemcpyAsync(centroids, w.sums, (size_t)n_c * kDim * 4, hipMemcpyDeviceToDevice, s),
+                     "copying the starting vectors");
+    if (rc) return done(rc);
+    launch_check_build(centroids, n_centroids, sample_ids, n_sample, N, w.first, s);
     launch_check_queries(tokens, N, err, s);
     launch_check_docs(token_docs, N, n_docs, err, s);
     int32_t herr = 0;
-    HIP_TRY(hipMemcpyAsync(&herr, err, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    unsigned long long first[2];
+    rc = try_hip(hipMemcpyAsync(&herr, err, 4, hipMemcpyDeviceToHost, s), "reading the checks");
+    if (!rc) rc = try_hip(hipMemcpyAsync(first, w.first, 16, hipMemcpyDeviceToHost, s), "reading the checks");
+    if (!rc) rc = try_hip(hipStreamSynchronize(s), "checking the inputs");
+    if (rc) return done(rc);
+    if (first[0] != ~0ull) {
+        const long long c = (long long)(first[0] >> 1);
+        return done((first[0] & 1) ? fail(WARP_EINVAL, "starting vector %lld is zero or too large", c)
+                                   : fail(WARP_EINVAL, "starting vector %lld is not finite", c));
+    }
+    if (first[1] != ~0ull)
+        return done(fail(WARP_EINVAL, "sample id %lld is out of range", (long long)first[1]));
     if (herr & kErrQueryNorm) return done(fail(WARP_EINVAL, "a token is not finite or has norm > 1 + 1e-3"));
     if (herr & kErrDocRange) return done(fail(WARP_EINVAL, "a token's document id is outside [0, n_docs)"));
 
-    HIP_TRY(hipMemcpyAsync(centroids, hC.data(), hC.size() * 4, hipMemcpyHostToDevice, s));
     launch_normalize_rows(centroids, n_centroids, s);  // the starting centroids
     auto assign_rows = [&](const float* x, int64_t n, int32_t* out) {
-        for (int64_t t0 = 0; t0 < n; t0 += chunk) {
-            const int64_t nt = std::min(chunk, n - t0);
-            launch_filter_gemm(x + t0 * kDim, (int32_t)nt, centroids, n_centroids, nullptr, (float*)w.scores.p, s);
-            launch_rows_argmax((const float*)w.scores.p, nt, n_centroids, x + t0 * kDim, centroids, out + t0, err, s);
-        }
+        launch_assign(x, n, centroids, n_centroids, w.match, out, err, s);
     };
     // k-means on the sample
-    float* xs = (float*)w.xs.p;
+    float* xs = w.xs;
     launch_gather_rows(tokens, sample_ids, n_sample, xs, s);
-    auto* sums = (unsigned long long*)w.sums.p;
-    auto* counts = (unsigned long long*)w.counts.p;
+    auto *sums = w.sums, *counts = w.counts;
     for (int it = 0; it < iterations; ++it) {
-        assign_rows(xs, n_sample, (int32_t*)w.assign_s.p);
+        assign_rows(xs, n_sample, w.assign_s);
         launch_fill_i32((int32_t*)sums, n_c * kDim * 2, 0, s);
         launch_fill_i32((int32_t*)counts, (n_c + 1) * 2, 0, s);
-        launch_kmeans_accum(xs, (const int32_t*)w.assign_s.p, n_sample, sums, counts, s);
+        launch_kmeans_accum(xs, w.assign_s, n_sample, sums, counts, s);
         launch_kmeans_normalize(sums, counts, n_centroids, centroids, s);
     }
     // every token to its nearest centroid; quantiles of the first n_quant tokens' residuals
     assign_rows(tokens, N, assign);
-    launch_residuals(tokens, assign, n_quant, centroids, (float*)w.resid.p, s);
-    if (sort_floats(w.temp.p, &tb, (const float*)w.resid.p, (float*)w.sorted.p, n_quant * kDim, s) != hipSuccess)
+    launch_residuals(tokens, assign, n_quant, centroids, w.resid, s);
+    if (sort_floats(w.temp, &tb, w.resid, w.sorted, n_quant * kDim, s) != hipSuccess)
         return done(fail(WARP_EDEVICE, "residual sort failed"));
-    launch_pick_quantiles((const float*)w.sorted.p, n_quant * kDim, nbits, bucket_cutoffs, bucket_weights, s);
+    launch_pick_quantiles(w.sorted, n_quant * kDim, nbits, bucket_cutoffs, bucket_weights, s);
     // embeddings grouped by cluster in input order, offsets, codes
-    launch_iota64((int64_t*)w.perm_in.p, N, s);
-    tb = w.temp.bytes;
-    if (sort_by_cluster(w.temp.p, &tb, assign, (int32_t*)w.keys.p, (const int64_t*)w.perm_in.p, (int64_t*)w.perm.p, N,
+    launch_iota64(w.perm_in, N, s);
+    tb = temp_bytes;
+    if (sort_by_cluster(w.temp, &tb, assign, w.keys, w.perm_in, w.perm, N,
                         end_bit, s) != hipSuccess)
         return done(fail(WARP_EDEVICE, "cluster sort failed"));
     launch_fill_i32((int32_t*)counts, (n_c + 1) * 2, 0, s);
     launch_count_clusters(assign, N, counts, s);
-    tb = w.temp.bytes;
-    if (exclusive_sum_u64(w.temp.p, &tb, counts, cluster_offsets, n_c + 1, s) != hipSuccess)
+    tb = temp_bytes;
+    if (exclusive_sum_u64(w.temp, &tb, counts, cluster_offsets, n_c + 1, s) != hipSuccess)
         return done(fail(WARP_EDEVICE, "offset scan failed"));
-    launch_encode(nbits, tokens, token_docs, assign, (const int64_t*)w.perm.p, N, centroids, bucket_cutoffs, codes,
+    launch_encode(nbits, tokens, token_docs, assign, w.perm, N, centroids, bucket_cutoffs, codes,
                   doc_ids, s);
-    HIP_TRY(hipMemcpyAsync(&herr, err, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    rc = try_hip(hipMemcpyAsync(&herr, err, 4, hipMemcpyDeviceToHost, s), "reading the result's flags");
+    if (!rc) rc = try_hip(hipStreamSynchronize(s), "index build");
+    if (rc) return done(rc);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return done(fail(WARP_EDEVICE, "index build failed: %s", hipGetErrorString(le)));
     if (herr & kErrArgOverflow)

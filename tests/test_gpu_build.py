@@ -77,6 +77,42 @@ def test_build_edge_cases():
     got, _ = _build_both(X, docs, len(lens), C1, sample, 2, 4, 200, label="duplicate centroids")
 
 
+@pytest.mark.parametrize("n_c", [1, 127, 129, 640])
+def test_build_nearest_centroid_blocks(n_c):
+    """The nearest-centroid search works on tiles of 128 centroids and keeps two tiles per lane:
+    centroid counts around a tile's edge, and sets in which every third centroid coincides, so that
+    more tiles tie than a lane keeps (every centroid is then scored; ties go to the lowest id)."""
+    import paper_2501_17788_amd as w
+
+    data, X, docs, lens = _inputs(60, n_docs=500, max_len=40, n_c=64)
+    sample = w.sample_passages(lens, c=30.0, seed=1)
+    C0 = w.initial_centroids(X, sample, n_c, seed=2)
+    _build_both(X, docs, len(lens), C0, sample, 1, 4, 300, label=f"{n_c} centroids")
+    C0[1::3] = C0[0]
+    _build_both(X, docs, len(lens), C0, sample, 1, 2, 300, label=f"{n_c} centroids, a third of them equal")
+
+
+def test_build_refuses_too_many_equal_centroids():
+    """Centroids equal to a token's best are accepted up to 1,024; more are WARP_ENOTSUP."""
+    import torch
+
+    import paper_2501_17788_amd as w
+
+    data, X, docs, lens = _inputs(61, n_docs=200, max_len=20, n_c=64)
+    sample = np.arange(64, dtype=np.int64)
+    for n_equal in (1000, 1100):
+        C = np.repeat(X[:1], n_equal + 8, axis=0)
+        C[n_equal:] = X[100:108]
+        say(f"[{n_equal} equal centroids]")
+        if n_equal <= 1024:
+            _build_both(X[:300], docs[:300], len(lens), C, sample, 0, 4, 100, label=f"{n_equal} equal centroids")
+            continue
+        with pytest.raises(w.WarpError) as e:
+            w.build_index(torch.from_numpy(X[:300]).cuda(), torch.from_numpy(docs[:300]).cuda(), len(lens), C, sample, 0, 4,
+                          100)
+        assert e.value.code == w.ENOTSUP
+
+
 def test_build_errors():
     import torch
 
