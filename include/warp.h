@@ -162,13 +162,14 @@ int warp_index_info(const warp_index* idx, int32_t* n_centroids, int64_t* n_embe
  *   queries      [n_queries][n_qtok][dim] fp32 host, each token of norm <= 1 + 1e-3
  *   n_queries    >= 1
  *   n_qtok       1..32 (query_maxlen = 32); every token takes part in the sum
- *   nprobe       1..n_centroids. Up to 256 the selection rescores only the
+ *   nprobe       1..n_centroids. Up to 512 the selection rescores only the
  *                centroids near its boundaries; above, it sorts every
- *                (token, centroid) score of a wave (same results, slower;
- *                WARP_ENOTSUP if n_qtok * n_centroids > 2^31)
+ *                (token, centroid) score of a wave (same results, slower).
+ *                Above 256, WARP_ENOTSUP if n_qtok * n_centroids > 2^31
  *   t_prime      >= 0, in embeddings
- *   k            >= 1. Up to 4096 the top-k gathers the best keys in LDS;
- *                above, it sorts every document key of a query (same results)
+ *   k            >= 1. Up to 4096 (up to 16384 if n_docs <= 2^18) the top-k
+ *                gathers the best keys in LDS; above, it sorts every document
+ *                key of a query (same results)
  *   out_doc_ids  [n_queries][k] caller-owned host; -1 past the result count
  *   out_scores   [n_queries][k] caller-owned host; -inf past the result count
  *   out_counts   [n_queries] host or NULL: min(k, number of candidate documents)
@@ -210,8 +211,8 @@ int warp_search_async(warp_index* idx, const float* queries, int32_t n_queries, 
  * that GPU until the process ends. A search takes waves of as many queries as
  * the array holds; if one query does not fit (roughly 4 * n_qtok * n_docs +
  * 2 * n_qtok * n_centroids + 8 * n_docs bytes, e.g. about 17 MB for 100k
- * documents, 1.1 GB for 8.8M; nprobe above 256 adds about 57 * n_qtok *
- * n_centroids bytes, k above 4096 about 25 * n_docs) it fails with WARP_ENOMEM
+ * documents, 1.1 GB for 8.8M; nprobe above 512 adds about 57 * n_qtok *
+ * n_centroids bytes, k that sorts every key about 25 * n_docs) it fails with WARP_ENOMEM
  * before enqueuing anything. Every call on a GPU shares that GPU's array, whichever index it
  * searches, and finds what the last call left there (the call clears what must
  * start at zero): calls that overlap on one GPU race, so enqueue them on one

@@ -11,8 +11,12 @@ namespace warp {
 constexpr int kDim = 128;          // token embedding dimension
 constexpr int kFrac = 26;          // fixed-point fraction bits of token and doc scores
 constexpr int kMaxQtok = 32;       // query_maxlen
-constexpr int kMaxProbe = 256;     // largest n_probe of the band selection; above, the sorting one
-constexpr int kMaxK = 4096;        // largest k of the LDS top-k; above, every key is sorted
+constexpr int kMaxProbe = 256;     // largest n_probe whose selection reports a band overflow as an error
+constexpr int kBandProbe = 512;    // largest n_probe of the band selection (above kMaxProbe a token whose band
+                                   // overflows is selected from all its scores); above, the sorting one
+constexpr int kMaxK = 4096;        // largest k of the LDS top-k with a list of blocks
+constexpr int kMaxKLarge = 16384;  // largest k of the LDS top-k without one; above, every key is sorted
+constexpr int kMaxKDocs = 1 << 18; // most documents of the latter (one workgroup reads a query's keys three times)
 constexpr int kMaxDocs = 1 << 24;  // document ids packed into the low 24 bits of a sort key
 constexpr int kTopkListCap = 4096;  // blocks of 256 documents the top-k's pruned passes can list
 // A token-max cell holds t plus the bias of its query's epoch (an order-preserving bias, see
@@ -101,6 +105,7 @@ struct WaveArgs {
     int32_t* sel_lists;         // [n_tok][2][kSelCap] centroids of the two rescoring bands
     int32_t* sel_cnt;           // [n_tok][2] their counts (may exceed kSelCap), zeroed per wave
     int32_t sel_slices;         // workgroups per token of the split selection; 1: one workgroup
+    int32_t sel_rest;           // a token whose band overflows gets sel[0] = -2 (launch_select_rest), not an error
     int32_t* ccount;            // [n_c] probing tokens per cluster
     int32_t* cursor;            // [n_c] scatter cursors
     int32_t* pair_start;        // [n_c] exclusive prefix of pairs within the cluster's block of
@@ -170,6 +175,7 @@ void launch_topk(const WaveArgs& a, hipStream_t s);
 // exact whole-list paths for n_probe > kMaxProbe and k > kMaxK (device radix sorts); the
 // scratch holds the bytes the *_bytes functions give
 size_t select_full_bytes(int64_t n_tok, int32_t n_c);
+void launch_select_rest(const WaveArgs& a, hipStream_t s);
 hipError_t launch_select_full(const WaveArgs& a, void* scratch, hipStream_t s);
 size_t topk_full_bytes(int32_t n_docs);
 hipError_t launch_topk_full(const WaveArgs& a, void* scratch, hipStream_t s);

@@ -95,7 +95,7 @@ struct warp_index {
     DevBuf list_rec, list_item, cblk;  // the wave's probed chunks (see WaveArgs)
     DevBuf list_rec2;                  // the wave's probed chunks of the narrow scan
     DevBuf scan_queue;
-    DevBuf full_sel, full_topk;  // sort scratch of the sorting selection and of k > kMaxK
+    DevBuf full_sel, full_topk;  // sort scratch of the sorting selection and top-k
     DevBuf sel_hist, sel_lists, sel_cnt;  // split selection of small waves
     bool force_full_select = false;       // the blocking search's retry after a selection overflow
     int32_t scoring = WARP_SCORING_PAPER;
@@ -482,8 +482,15 @@ void clear_slots(warp_index* idx, hipStream_t s) {
 }
 
 // The selection sorts whole score lists (instead of rescoring the boundary bands) for n_probe
-// above kMaxProbe, and in the blocking search's retry after a band overflowed.
-bool full_select(const warp_index* idx, int32_t P) { return P > kMaxProbe || idx->force_full_select; }
+// above kBandProbe, and in the blocking search's retry after a band overflowed.
+bool full_select(const warp_index* idx, int32_t P) { return P > kBandProbe || idx->force_full_select; }
+
+// The top-k sorts every document key of a query for k above kMaxKLarge, and above kMaxK where one
+// workgroup would read too many keys (100k documents, k = 5,000, 8 queries: 2.30 ms of sorts, one
+// query after another, against 0.17 ms).
+bool full_topk(const warp_index* idx, int32_t k) {
+    return k > kMaxKLarge || (k > kMaxK && idx->n_docs > kMaxKDocs);
+}
 
 // Workgroups per token of the selection for a wave of n_tok tokens: one for large waves; for
 // waves of at most kSplitTokens tokens, enough to give every compute unit three workgroups, with
@@ -533,7 +540,7 @@ int reserve(warp_index* idx, int32_t qw, int32_t T, int32_t P, int32_t k, hipStr
     if (!rc) rc = grow_scratch(idx, idx->cblk, (size_t)cblocks * 24);
     if (!rc) rc = grow_scratch(idx, idx->scan_queue, 256);
     if (!rc && full_select(idx, P)) rc = grow_scratch(idx, idx->full_sel, select_full_bytes(n_tok, idx->n_c));
-    if (!rc && k > kMaxK) rc = grow_scratch(idx, idx->full_topk, topk_full_bytes(idx->n_docs));
+    if (!rc && full_topk(idx, k)) rc = grow_scratch(idx, idx->full_topk, topk_full_bytes(idx->n_docs));
     const int64_t st = split_tokens(idx, n_tok);
     if (!rc) rc = grow_scratch(idx, idx->sel_hist, (size_t)st * kSelBins * 8);
     if (!rc) rc = grow_scratch(idx, idx->sel_lists, (size_t)st * 2 * kSelCap * 4);
@@ -688,7 +695,7 @@ struct WaveScratch {
     int4 *list_rec, *list_rec2;
     int64_t *list_item, *cblk;
     uint32_t* scan_queue;
-    void *full_sel, *full_topk;  // sort scratch of the sorting selection and of k > kMaxK
+    void *full_sel, *full_topk;  // sort scratch of the sorting selection and top-k
     unsigned long long* sel_hist;  // split selection: histograms, band lists and counts of up
     int32_t *sel_lists, *sel_cnt;  // to split_cap tokens
     int64_t split_cap;
@@ -795,6 +802,7 @@ hipError_t launch_wave(warp_index* idx, const WaveScratch& w, const float* dq, i
     a.narrow_max = narrow_max(nq);
     const int64_t n_tok = (int64_t)nq * T;
     a.sel_slices = n_tok <= w.split_cap ? select_slices(idx, n_tok) : 1;
+    a.sel_rest = P > kMaxProbe;
     a.sel_hist = w.sel_hist;
     a.sel_lists = w.sel_lists;
     a.sel_cnt = w.sel_cnt;
@@ -819,7 +827,10 @@ hipError_t launch_wave(warp_index* idx, const WaveScratch& w, const float* dq, i
     launch_wave_prep(a, epochs ? (uint32_t*)idx->q_epoch.p : nullptr, (uint32_t)idx->tab_epochs, s);
     hipError_t err = hipSuccess;
     if (full_select(idx, P)) err = launch_select_full(a, w.full_sel, s);
-    else launch_select(a, s);
+    else {
+        launch_select(a, s);
+        if (a.sel_rest) launch_select_rest(a, s);
+    }
     mark(2);
     launch_scored(a, s);
     launch_pairing(a, s);
@@ -829,7 +840,7 @@ hipError_t launch_wave(warp_index* idx, const WaveScratch& w, const float* dq, i
     mark(4);
     launch_fold(a, s);
     mark(5);
-    if (k > kMaxK) {
+    if (full_topk(idx, k)) {
         const hipError_t e = launch_topk_full(a, w.full_topk, s);
         if (err == hipSuccess) err = e;
     } else {
@@ -845,7 +856,7 @@ hipError_t launch_wave(warp_index* idx, const WaveScratch& w, const float* dq, i
 // Enqueue a whole search on `s`; every pointer is device memory.
 int enqueue_search(warp_index* idx, const float* dq, int32_t n_queries, int32_t T, int32_t P,
                    int64_t t_prime, int32_t k, const SearchOut& o, hipStream_t s) {
-    if (full_select(idx, P) && (int64_t)T * idx->n_c > ((int64_t)1 << 31))
+    if ((P > kMaxProbe || idx->force_full_select) && (int64_t)T * idx->n_c > ((int64_t)1 << 31))
         return fail(WARP_ENOTSUP, "the sorted selection needs n_qtok * n_centroids <= 2^31");
     const int32_t qw = wave_queries(idx, n_queries, T, P);
     int rc = reserve(idx, qw, T, P, k, s);
@@ -965,8 +976,8 @@ size_t noalloc_layout(const warp_index* idx, int32_t qw, int32_t T, int32_t P, i
     w.tokmax = (uint32_t*)take(n_tok * nd * 4);
     w.tokcnt = literal ? (uint32_t*)take(n_tok * nd * 4) : nullptr;
     w.q_epoch = nullptr;  // cells hold t + 2^31 and the fold resets every cell it reads
-    w.full_sel = P > kMaxProbe ? take(select_full_bytes((int64_t)n_tok, idx->n_c)) : nullptr;
-    w.full_topk = k > kMaxK ? take(topk_full_bytes(idx->n_docs)) : nullptr;
+    w.full_sel = P > kBandProbe ? take(select_full_bytes((int64_t)n_tok, idx->n_c)) : nullptr;
+    w.full_topk = full_topk(idx, k) ? take(topk_full_bytes(idx->n_docs)) : nullptr;
     w.split_cap = split_tokens(idx, (int64_t)n_tok);
     w.sel_hist = (unsigned long long*)take((size_t)w.split_cap * kSelBins * 8);
     w.sel_lists = (int32_t*)take((size_t)w.split_cap * 2 * kSelCap * 4);
@@ -999,7 +1010,7 @@ int warp_search_noalloc(warp_index* idx, const float* queries, int32_t n_queries
     // the largest wave that fits (the layout grows with the wave); the exact selection
     // sorts at most 2^31 scores per wave
     int32_t lo = 1, hi = n_queries;
-    if (nprobe > kMaxProbe) hi = (int32_t)std::min<int64_t>(hi, ((int64_t)1 << 31) / ((int64_t)n_qtok * idx->n_c));
+    if (nprobe > kBandProbe) hi = (int32_t)std::min<int64_t>(hi, ((int64_t)1 << 31) / ((int64_t)n_qtok * idx->n_c));
     while (lo < hi) {
         const int32_t mid = lo + (hi - lo + 1) / 2;
         if (noalloc_layout(idx, mid, n_qtok, nprobe, k, literal, nullptr, nullptr) <= kNoAllocBytes) lo = mid;

@@ -1,5 +1,5 @@
 // Exact paths for requests beyond what the selection and top-k kernels hold in LDS
-// (n_probe above kMaxProbe, k above kMaxK, and a selection band of more than kSelCap
+// (n_probe above kBandProbe, k above kMaxKLarge or, with many documents, kMaxK, and a selection band of more than kSelCap
 // centroids in the blocking search's retry): whole score lists are sorted with the device
 // radix sort, which gives the definitions of Sections 4.3 and 4.5 directly.
 //
@@ -9,7 +9,7 @@
 // centroids, their fixed-point scores and size prefix, and m_i = the score of the first
 // entry whose inclusive cumulative size exceeds t' (the last entry when none does).
 //
-// Top-k (Section 4.5) for k > kMaxK: every document key of the query (the fold's, larger
+// Top-k (Section 4.5) for such k: every document key of the query (the fold's, larger
 // is better, 0 for a non-candidate) sorted in descending order; the first min(k, #candidates)
 // are decoded.
 #include <algorithm>

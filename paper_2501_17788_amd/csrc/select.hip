@@ -337,7 +337,11 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
     // from step 4 on, hist holds the sizes of the rescored centroids
     int* const szA = reinterpret_cast<int*>(hist);
     int* const szB = szA + kSelCap;
-    static_assert(2 * kSelCap * sizeof(int) <= sizeof(hist), "sizes must fit the histogram's LDS");
+    // and the selected centroids and their fixed-point scores by rank (scores that are not numbers,
+    // of a token that the norm check refuses, leave ranks empty: no centroid)
+    int* const s_sel = szB + kSelCap;
+    int* const s_base = s_sel + kSelCap;
+    static_assert(4 * kSelCap * sizeof(int) <= sizeof(hist), "must fit the histogram's LDS");
     __shared__ int s_nA, s_nB, s_cross;
     __shared__ unsigned long long s_band_above;
 
@@ -415,14 +419,21 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
             base[j] = 0;
         }
         for (int j = tid; j <= P; j += NT) seg_pref[j] = 0;
+        __syncthreads();
         if (tid == 0) {
             a.m_fixed[t] = 0;
-            atomicOr(a.err, kErrSelOverflow);
+            if (a.sel_rest) sel[0] = -2;
+            else atomicOr(a.err, kErrSelOverflow);
         }
         return;
     }
 
     // 4. fp64 rescoring of both lists, four lanes per centroid; the sizes come in beside
+    for (int j = tid; j < P; j += NT) {
+        s_sel[j] = -1;
+        s_base[j] = 0;
+        cum[j] = 0;
+    }
     for (int p = tid >> 2; p < nA + nB; p += NT / 4) {  // uniform over each four lanes
         const int c = p < nA ? idA[p] : idB[p - nA];
         int sz;
@@ -445,14 +456,18 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
     rank_all(sA, idA, nA, [&](int p, int r) {
         if (r < P) {
             const int c = idA[p];
-            sel[r] = c;
+            s_sel[r] = c;
             atomicAdd(&a.ccount[c], 1);
-            base[r] = (int32_t)to_fixed(sA[p]);
+            s_base[r] = (int32_t)to_fixed(sA[p]);
             cum[r] = szA[p];
-            if (a.dbg_sel) a.dbg_sel[(int64_t)t * P + r] = c;
         }
     });
     __syncthreads();
+    for (int j = tid; j < P; j += NT) {
+        sel[j] = s_sel[j];
+        base[j] = s_base[j];
+        if (a.dbg_sel) a.dbg_sel[(int64_t)t * P + j] = s_sel[j];
+    }
     block_inclusive_scan(cum, P, wtot);
     for (int j = tid; j <= P; j += NT) seg_pref[j] = j == 0 ? 0 : cum[j - 1];
     __syncthreads();
@@ -481,6 +496,146 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
         a.m_fixed[t] = to_fixed(m);
         if (a.dbg_m) a.dbg_m[t] = to_fixed(m);
     }
+}
+
+// Selection of the tokens that k_select left (sel[0] = -2: a band of more than kSelCap centroids,
+// only with degenerate centroid sets), for P <= kSelCap: one workgroup per token over all its fp64
+// scores, recomputed in every pass. An MSB-first radix select over the order-reversing 64-bit score
+// keys, then over the ids among equal scores, finds the P-th centroid in (score desc, id asc)
+// order; another, over the sizes, the key of the first centroid whose inclusive size sum exceeds
+// t' (the highest key where the total does not). The P first are gathered and ranked. (Other tokens' workgroups exit at once.)
+__global__ __launch_bounds__(kSelThreads) void k_select_rest(WaveArgs a) {
+    constexpr int NT = kSelThreads;
+    __shared__ unsigned long long hist[256], whist[256];
+    __shared__ unsigned long long wtot[NT / 64];
+    __shared__ float qs[kDim];
+    __shared__ double sA[kSelCap];
+    __shared__ int idA[kSelCap];
+    __shared__ int64_t cum[kSelCap];
+    __shared__ unsigned long long s_pre, s_wpre, s_need, s_wabove;
+    __shared__ int s_n;
+    const int t = blockIdx.x, tid = threadIdx.x;
+    const int n_c = a.n_c, P = a.nprobe;
+    int32_t* sel = a.sel + (int64_t)t * P;
+    if (sel[0] != -2) return;  // uniform
+    const unsigned long long tp = (unsigned long long)a.t_prime;
+    if (tid < kDim) qs[tid] = a.queries[(int64_t)t * kDim + tid];
+    __syncthreads();
+    auto score = [&](int c) {
+        const float* row = a.centroids + (int64_t)c * kDim;
+        double v = 0.0;
+        for (int d = 0; d < kDim; ++d) v = __builtin_fma((double)row[d], (double)qs[d], v);  // exact products
+        return v;
+    };
+    // ascending order of the keys is descending order of the scores
+    auto key_of = [](double x) {
+        unsigned long long b = (unsigned long long)__double_as_longlong(x);
+        b = (b >> 63) ? ~b : (b | (1ull << 63));
+        return ~b;
+    };
+    if (tid == 0) {
+        s_pre = 0;
+        s_wpre = 0;
+        s_need = (unsigned long long)P;
+        s_wabove = 0;
+        s_n = 0;
+    }
+    __syncthreads();
+    for (int shift = 56; shift >= 0; shift -= 8) {
+        for (int i = tid; i < 256; i += NT) {
+            hist[i] = 0;
+            whist[i] = 0;
+        }
+        __syncthreads();
+        const unsigned long long pre = s_pre, wpre = s_wpre;
+        const unsigned long long mask = shift == 56 ? 0 : ~0ull << (shift + 8);
+        for (int c = tid; c < n_c; c += NT) {
+            const unsigned long long k = key_of(score(c));
+            if ((k & mask) == pre) atomicAdd(&hist[(k >> shift) & 255], 1ull);
+            // (the count beside the size: an empty cluster may hold the highest key)
+            if ((k & mask) == wpre) atomicAdd(&whist[(k >> shift) & 255], kCntOne | (unsigned long long)a.sizes[c]);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            unsigned long long run = 0;
+            int d = 0;
+            while (run + hist[d] < s_need) run += hist[d++];
+            s_need -= run;
+            s_pre = pre | ((unsigned long long)d << shift);
+            unsigned long long w = s_wabove;
+            int e = -1, last = 0;
+            for (int i = 0; i < 256; ++i) {
+                if (whist[i]) last = i;
+                if (e < 0 && w + (whist[i] & kSizeMask) > tp) e = i;
+                if (e < 0) w += whist[i] & kSizeMask;
+            }
+            if (e >= 0) s_wabove = w;
+            s_wpre = wpre | ((unsigned long long)(e >= 0 ? e : last) << shift);
+        }
+        __syncthreads();
+    }
+    // ids among the centroids of the P-th key: the s_need lowest
+    unsigned ipre = 0;
+    const unsigned long long kth = s_pre;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        for (int i = tid; i < 256; i += NT) hist[i] = 0;
+        __syncthreads();
+        const unsigned imask = shift == 24 ? 0u : ~0u << (shift + 8);
+        for (int c = tid; c < n_c; c += NT)
+            if (((unsigned)c & imask) == ipre && key_of(score(c)) == kth) atomicAdd(&hist[((unsigned)c >> shift) & 255], 1ull);
+        __syncthreads();
+        if (tid == 0) {
+            unsigned long long run = 0;
+            int d = 0;
+            while (run + hist[d] < s_need) run += hist[d++];
+            s_need -= run;
+            wtot[0] = (unsigned long long)d;
+        }
+        __syncthreads();
+        ipre |= (unsigned)wtot[0] << shift;
+        __syncthreads();
+    }
+    for (int c = tid; c < n_c; c += NT) {
+        const double v = score(c);
+        const unsigned long long k = key_of(v);
+        if (k < kth || (k == kth && (unsigned)c <= ipre)) {
+            const int p = atomicAdd(&s_n, 1);  // P of them
+            sA[p] = v;
+            idA[p] = c;
+        }
+        if (k == s_wpre) {  // every such centroid has the score m_i
+            a.m_fixed[t] = to_fixed(v);
+            if (a.dbg_m) a.dbg_m[t] = to_fixed(v);
+        }
+    }
+    int32_t* base = a.base + (int64_t)t * P;
+    int64_t* seg_pref = a.seg_pref + (int64_t)t * (P + 1);
+    __shared__ int s_sel[kSelCap], s_base[kSelCap];
+    for (int j = tid; j < P; j += NT) {  // (ranks of scores that are not numbers stay empty)
+        s_sel[j] = -1;
+        s_base[j] = 0;
+        cum[j] = 0;
+    }
+    __syncthreads();
+    rank_all(sA, idA, P, [&](int p, int r) {
+        const int c = idA[p];
+        s_sel[r] = c;
+        atomicAdd(&a.ccount[c], 1);
+        s_base[r] = (int32_t)to_fixed(sA[p]);
+        cum[r] = a.sizes[c];
+    });
+    __syncthreads();
+    for (int j = tid; j < P; j += NT) {
+        sel[j] = s_sel[j];
+        base[j] = s_base[j];
+        if (a.dbg_sel) a.dbg_sel[(int64_t)t * P + j] = s_sel[j];
+    }
+    block_inclusive_scan(cum, P, wtot);
+    for (int j = tid; j <= P; j += NT) seg_pref[j] = j == 0 ? 0 : cum[j - 1];
+}
+
+void launch_select_rest(const WaveArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_select_rest, dim3(a.n_q * a.n_qtok), dim3(kSelThreads), 0, s, a);
 }
 
 void launch_select(const WaveArgs& a, hipStream_t s) {

@@ -16,7 +16,7 @@
 // K largest keys are found in one or two histogram passes over the keys: bins of the
 // distance below the largest score (4096 bins of 2^-6, then, inside the bin holding the
 // K-th key, 4096 bins of 2^-18), after which every key at or above the bin holding the
-// K-th key is gathered (at most kMaxK); each takes its rank among them as its position
+// K-th key is gathered (at most CAP); each takes its rank among them as its position
 // (up to kRankMax keys), or they are sorted in LDS, and the first K are decoded. When
 // the K-th key lies more than 64 below the best, or its fine bin alone would overflow
 // the gather buffer, an MSB-first radix select over the whole key (8 bits per pass)
@@ -71,7 +71,8 @@ __device__ void find_crossing(const uint32_t* hist, uint32_t need, uint32_t* sca
 }
 
 // Appends key to buf[*count] where pred holds, with one LDS atomic per wave for the lanes
-// that call it together; positions past kMaxK are counted but not written.
+// that call it together; positions past CAP are counted but not written.
+template <int CAP>
 __device__ __forceinline__ void append_key(bool pred, unsigned long long key, uint32_t* count,
                                            unsigned long long* buf) {
     const unsigned long long m = __ballot(pred);
@@ -83,15 +84,19 @@ __device__ __forceinline__ void append_key(bool pred, unsigned long long key, ui
     base = __shfl(base, leader, 64);
     if (pred) {
         const uint32_t p = base + (uint32_t)__popcll(m & ((1ull << lane) - 1));
-        if (p < (uint32_t)kMaxK) buf[p] = key;
+        if (p < (uint32_t)CAP) buf[p] = key;
     }
 }
 
+// CAP: keys of the gather buffer. With kMaxK the block list fits LDS beside it; with kMaxKLarge
+// (k above kMaxK) every block is visited.
+template <int CAP>
 __global__ __launch_bounds__(kTopkThreads) void k_topk(WaveArgs a) {
+    constexpr bool LIST = CAP == kMaxK;
     __shared__ uint32_t hist[kTopkBins];
     __shared__ uint32_t scan[kTopkThreads / 64];
-    __shared__ unsigned long long buf[kMaxK];
-    __shared__ int32_t blist[kTopkListCap];
+    __shared__ unsigned long long buf[CAP];
+    __shared__ int32_t blist[LIST ? kTopkListCap : 1];
     __shared__ unsigned long long s_prefix, s_mask, s_max, s_lim;
     __shared__ uint32_t s_need, s_count, s_ncand, s_before, s_nlist;
     __shared__ int s_bin;
@@ -154,7 +159,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(WaveArgs a) {
     bool done = K == 0;
     // D0 from the block maxima: coarse bins, then fine bins inside the crossing one
     unsigned long long d0 = 0;  // 0: no pruning
-    if (!done) {
+    if (LIST && !done) {
         for (int i = tid; i < kTopkBins; i += kTopkThreads) hist[i] = 0;
         __syncthreads();
         for_each_part([&](int64_t, unsigned long long, unsigned long long mx) {
@@ -218,10 +223,10 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(WaveArgs a) {
         for_each_key([&](unsigned long long key) {
             const unsigned long long d = smax - (key >> 24);
             if (d < ((unsigned long long)kTopkBins << kCoarseShift)) atomicAdd(&hist[d >> kCoarseShift], 1u);
-            if (spec) append_key(d < d0, key, &s_count, buf);
+            if (spec) append_key<CAP>(d < d0, key, &s_count, buf);
         });
         __syncthreads();
-        if (spec && s_count <= (uint32_t)kMaxK) done = true;  // uniform
+        if (spec && s_count <= (uint32_t)CAP) done = true;  // uniform
         else if (spec) {
             __syncthreads();  // every thread has read s_count
             if (tid == 0) s_count = 0;
@@ -233,7 +238,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(WaveArgs a) {
         if (b1 >= 0) {
             const uint32_t above = s_before;
             unsigned long long lim = 0;  // gather every key with distance < lim
-            if (above + hist[b1] <= (uint32_t)kMaxK) {
+            if (above + hist[b1] <= (uint32_t)CAP) {
                 lim = (unsigned long long)(b1 + 1) << kCoarseShift;
             } else {
                 // level 2: fine bins inside coarse bin b1
@@ -249,14 +254,14 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(WaveArgs a) {
                 __syncthreads();
                 find_crossing(hist, (uint32_t)K - above, scan, &s_bin, &s_before);
                 const int b2 = s_bin;
-                if (b2 >= 0 && above + s_before + hist[b2] <= (uint32_t)kMaxK)
+                if (b2 >= 0 && above + s_before + hist[b2] <= (uint32_t)CAP)
                     lim = base + ((unsigned long long)(b2 + 1) << kFineShift);
             }
             if (tid == 0) s_lim = lim;
             __syncthreads();
             lim = s_lim;
             if (lim != 0) {
-                for_each_key([&](unsigned long long key) { append_key(smax - (key >> 24) < lim, key, &s_count, buf); });
+                for_each_key([&](unsigned long long key) { append_key<CAP>(smax - (key >> 24) < lim, key, &s_count, buf); });
                 done = true;
             }
         }
@@ -296,10 +301,10 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(WaveArgs a) {
             __syncthreads();
         }
         const unsigned long long kth = s_prefix;  // the K-th largest key
-        for_each_key([&](unsigned long long key) { append_key(key >= kth, key, &s_count, buf); });
+        for_each_key([&](unsigned long long key) { append_key<CAP>(key >= kth, key, &s_count, buf); });
         __syncthreads();
     }
-    const int cnt = K == 0 ? 0 : (int)(s_count < (uint32_t)kMaxK ? s_count : (uint32_t)kMaxK);
+    const int cnt = K == 0 ? 0 : (int)(s_count < (uint32_t)CAP ? s_count : (uint32_t)CAP);
     auto emit = [&](int r, unsigned long long key) {  // output position r < K
         const int64_t o = (int64_t)q * a.k + r;
         const int32_t doc = (int32_t)(kMaxDocs - 1 - (int32_t)(key & (kMaxDocs - 1)));
@@ -323,21 +328,30 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(WaveArgs a) {
         for (int i = tid; i < np; i += kTopkThreads)
             if (i >= cnt) buf[i] = 0;
         __syncthreads();
+        // pair p of a stage of distance j: elements e and e + j. Below a distance of 128 a wave's 64
+        // consecutive pairs stay inside its own 128 elements, so no barrier separates those stages.
+        auto exchange = [&](int p, int j, int kk) {
+            const int e = 2 * (p & ~(j - 1)) + (p & (j - 1));
+            const unsigned long long x = buf[e], y = buf[e + j];
+            if ((e & kk) == 0 ? x < y : x > y) {
+                buf[e] = y;
+                buf[e + j] = x;
+            }
+        };
         for (int kk = 2; kk <= np; kk <<= 1) {
-            for (int j = kk >> 1; j > 0; j >>= 1) {
-                for (int i = tid; i < np; i += kTopkThreads) {
-                    const int ixj = i ^ j;
-                    if (ixj > i) {
-                        const bool desc = (i & kk) == 0;
-                        const unsigned long long x = buf[i], y = buf[ixj];
-                        if (desc ? (x < y) : (x > y)) {
-                            buf[i] = y;
-                            buf[ixj] = x;
-                        }
-                    }
-                }
+            int j = kk >> 1;
+            for (; j > 64; j >>= 1) {
+                for (int p = tid; p < np / 2; p += kTopkThreads) exchange(p, j, kk);
                 __syncthreads();
             }
+            for (int p = tid; p < np / 2; p += kTopkThreads)
+                for (int jj = j; jj > 0; jj >>= 1) {
+                    exchange(p, jj, kk);
+                    __builtin_amdgcn_wave_barrier();
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_wave_barrier();
+                }
+            __syncthreads();
         }
         for (int r = tid; r < K; r += kTopkThreads) emit(r, buf[r]);
     }
@@ -351,7 +365,8 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(WaveArgs a) {
 }
 
 void launch_topk(const WaveArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_topk, dim3(a.n_q), dim3(kTopkThreads), 0, s, a);
+    if (a.k <= kMaxK) hipLaunchKernelGGL(k_topk<kMaxK>, dim3(a.n_q), dim3(kTopkThreads), 0, s, a);
+    else hipLaunchKernelGGL(k_topk<kMaxKLarge>, dim3(a.n_q), dim3(kTopkThreads), 0, s, a);
 }
 
 }  // namespace warp

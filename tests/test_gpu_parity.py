@@ -140,6 +140,45 @@ def test_large_nprobe_and_k(case):
         run_both(data, label=f"large seed {seed} literal", literal=True)
 
 
+@pytest.mark.parametrize("case", [
+    # n_centroids, n_docs, nprobe, k, t_prime, n_queries, n_qtok: the edges of the band selection
+    # (256, 512), of the top-k's gather buffers (4,096 and 16,384) and of its sort lengths
+    (3000, 6000, 257, 4097, 900, 3, 8), (1500, 20000, 512, 8193, 20000, 2, 32), (600, 9000, 512, 4096, 10 ** 9, 2, 5),
+    (3000, 20000, 400, 16384, 0, 3, 8), (700, 25000, 300, 16385, 5000, 2, 3), (3000, 6000, 513, 6000, 900, 2, 8)])
+def test_selection_and_topk_sizes(case):
+    n_c, n_docs, nprobe, k, tp, nq, nt = case
+    wl = synth.random_small_workload(5, n_centroids=n_c, n_docs=n_docs, max_len=12, nbits=4, n_queries=nq,
+                                     n_qtok=nt, nprobe=nprobe, t_prime=tp, k=k)
+    run_both(synth.make_index(wl, workers=1), label=f"sizes {case}")
+
+
+@pytest.mark.parametrize("t_prime", [0, 500, 20000, 10 ** 8])
+def test_wide_selection_of_equal_centroids(t_prime):
+    """nprobe above 256 with 2,001 identical centroids: tokens whose band of equal scores does not
+    fit are selected from all their scores (the lowest ids first), at the top and at the bottom of
+    the order, by the asynchronous search too."""
+    import dataclasses
+
+    import torch
+
+    w = _engine()
+    wl = synth.random_small_workload(30, n_centroids=3000, n_docs=2000, max_len=12, nbits=4, n_queries=3,
+                                     n_qtok=8, nprobe=300, t_prime=t_prime, k=20)
+    data = synth.make_index(wl, workers=1)
+    C = data.centroids.copy()
+    C[1:2001] = C[0]
+    Q = data.queries.copy()
+    Q[0, 0] = C[0]
+    Q[1, 1] = -C[0]
+    data = dataclasses.replace(data, centroids=C, queries=Q)
+    want = run_both(data, label=f"equal centroids t'={t_prime}")
+    with w.Index.from_synthetic(data) as ix:
+        ids, _, _, fixed = ix.search_async(torch.from_numpy(Q).cuda(), wl.nprobe, t_prime, wl.k)
+        ix.sync()
+        np.testing.assert_array_equal(ids.cpu().numpy(), want["ids"])
+        np.testing.assert_array_equal(fixed.cpu().numpy(), want["fixed"])
+
+
 def test_selection_band_overflow_falls_back_to_sorting():
     """2,000 identical centroids and a query token equal to them: all 2,000 share the top
     selection bin, more than the 1,024 that the band rescoring holds. The blocking search runs
@@ -585,7 +624,7 @@ def test_topk_ties_and_block_pruning(cap, monkeypatch):
     if cap is not None:
         monkeypatch.setenv("WARP_TOPK_LIST_BLOCKS", cap)
     arrays, Q = _tied_index()
-    for k in (4096, 100, 1):
+    for k in (5500, 4096, 100, 1):
         say(f"[topk ties cap={cap}] k={k}")
         with w.Index(**arrays) as ix:
             got = ix.search_debug(Q, 4, 0, k)
