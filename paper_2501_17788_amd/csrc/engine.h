@@ -46,6 +46,8 @@ __device__ __forceinline__ int score_bin(float f) {
 // embeddings, group of up to kMxGroup probing tokens), run by kMxBlock threads.
 constexpr int kMxChunk = 256;
 constexpr int kMxGroup = 32;
+constexpr int kMxGroupSmall = 16;   // in waves of at most kMxSmallTokens tokens (k_scan_small)
+constexpr int kMxSmallTokens = 32;
 constexpr int kMxBlock = 256;
 // The persistent scan grid takes its items in batches of kScanBatch consecutive items:
 // workgroup b starts with batch b, and every later batch comes from a device counter.
@@ -141,6 +143,7 @@ struct WaveArgs {
     uint32_t* dbg_bitmap;       // [n_q][ceil(n_docs / 32)] or null
     int64_t* dbg_scored;        // [n_q] or null
     int32_t scan_grid;          // persistent workgroups of the residual scan
+    int32_t mx_group;           // tokens per group of the wide scan: kMxGroup or kMxGroupSmall
     int32_t narrow_max;         // chunks probed by 1..narrow_max tokens take the narrow scan
     int32_t topk_list_cap;      // at most kTopkListCap; the top-k visits every block when more pass
 };
@@ -168,6 +171,8 @@ void launch_pairing(const WaveArgs& a, hipStream_t s);
 void launch_wave_prep(const WaveArgs& a, uint32_t* ep, uint32_t last, hipStream_t s);
 void launch_scan_mx(const WaveArgs& a, hipStream_t s);
 int scan_mx_blocks_per_cu(int nbits);
+int scan_small_blocks_per_cu(int nbits);
+void launch_scan_small(const WaveArgs& a, hipStream_t s);
 void launch_scan_narrow(const WaveArgs& a, int32_t grid, hipStream_t s);
 int scan_narrow_blocks_per_cu(int nbits);
 void launch_fold(const WaveArgs& a, hipStream_t s);

@@ -72,7 +72,8 @@ struct warp_index {
     float* weights = nullptr;
     int32_t* err = nullptr;
     hipStream_t stream = nullptr;
-    int scan_grid = 0;     // persistent workgroups of the residual scan
+    int scan_grid = 0;     // persistent workgroups of the wide scan
+    int small_grid = 0;    // of both scans in one launch (k_scan_small)
     int narrow_grid = 0;   // workgroups of the narrow scan (four waves, one chunk per wave at a time)
     int n_cu = 0;          // compute units of the device
     // per-search scratch, grown on demand
@@ -355,6 +356,7 @@ int finish_load(warp_index* idx, const int64_t* off_host) {
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, idx->device));
     idx->scan_grid = cus * scan_mx_blocks_per_cu(idx->nbits);
+    idx->small_grid = cus * scan_small_blocks_per_cu(idx->nbits);
     idx->n_cu = cus;
     idx->narrow_grid = cus * scan_narrow_blocks_per_cu(idx->nbits);
     return WARP_OK;
@@ -797,7 +799,9 @@ hipError_t launch_wave(warp_index* idx, const WaveScratch& w, const float* dq, i
     a.cblk = w.cblk;
     a.scan_queue = w.scan_queue;
     a.qdig = w.qdig;
-    a.scan_grid = idx->scan_grid;
+    const bool small = (int64_t)nq * T <= kMxSmallTokens;
+    a.mx_group = small ? kMxGroupSmall : kMxGroup;
+    a.scan_grid = small ? idx->small_grid : idx->scan_grid;
     a.topk_list_cap = topk_list_cap();
     a.narrow_max = narrow_max(nq);
     const int64_t n_tok = (int64_t)nq * T;
@@ -835,8 +839,12 @@ hipError_t launch_wave(warp_index* idx, const WaveScratch& w, const float* dq, i
     launch_scored(a, s);
     launch_pairing(a, s);
     mark(3);
-    launch_scan_mx(a, s);
-    launch_scan_narrow(a, idx->narrow_grid, s);
+    if (small) {
+        launch_scan_small(a, s);
+    } else {
+        launch_scan_mx(a, s);
+        if (a.narrow_max > 0) launch_scan_narrow(a, idx->narrow_grid, s);  // else its list is empty
+    }
     mark(4);
     launch_fold(a, s);
     mark(5);

@@ -1,7 +1,7 @@
 // Cluster-major work plan of one wave of queries: every (query token, probed
 // cluster) pair is bucketed by cluster (a counting sort whose counts the selection
 // takes), and each probed cluster is cut into work items of (kMxChunk embeddings) x
-// (kMxGroup tokens), so that the residual scan reads a cluster chunk once for all the
+// (mx_group tokens), so that the residual scan reads a cluster chunk once for all the
 // tokens that probe it. Pair order inside a bucket follows atomic arrival and does not
 // affect results: the token-level max is exact and commutative. Three launches: block
 // sums of the counts (with the pair offsets inside each block of clusters), their
@@ -85,7 +85,7 @@ __device__ __forceinline__ void chunk_items(const WaveArgs& a, int64_t j, int64_
     if (j < a.n_chunks) {
         const int32_t nt = a.ccount[a.chunk_c[j]];
         if (nt > a.narrow_max) {
-            items = (nt + kMxGroup - 1) / kMxGroup;
+            items = (nt + a.mx_group - 1) / a.mx_group;
             flag = 1;
         } else {
             narrow = nt > 0;

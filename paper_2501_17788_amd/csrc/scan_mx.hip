@@ -332,6 +332,7 @@ __device__ __forceinline__ T plan_load(const T* p, int64_t i) {
 
 // item of the wave's probed-chunk list entry p, whose record is rec (its chunk's token
 // group item - list_item[p])
+template <int G>
 __device__ __forceinline__ MxItem mx_decode(const v4i rec, int64_t item, int64_t item0) {
     MxItem it;
     const uint64_t ew = (uint64_t)(uint32_t)rec[0] | ((uint64_t)(uint32_t)rec[1] << 32);
@@ -339,8 +340,8 @@ __device__ __forceinline__ MxItem mx_decode(const v4i rec, int64_t item, int64_t
     const int nt = rec[3];
     it.e0 = (int64_t)(ew & ((1ull << kRecLenShift) - 1));
     it.e1 = it.e0 + (int64_t)(ew >> kRecLenShift);
-    it.p0 = rec[2] + grp * kMxGroup;
-    it.np = nt - grp * kMxGroup < kMxGroup ? nt - grp * kMxGroup : kMxGroup;
+    it.p0 = rec[2] + grp * G;
+    it.np = nt - grp * G < G ? nt - grp * G : G;
     return it;
 }
 
@@ -349,38 +350,54 @@ __device__ __forceinline__ MxItem mx_decode(const v4i rec, int64_t item, int64_t
 template <int QPT>
 struct MxStage {
     v4i q[QPT];     // query digit slots tid + kMxBlock i of the group
-    int tok, base;  // thread tid < kMxGroup: wave token and R(S64) + cell bias of group token tid
+    int tok, base;  // thread tid < G: wave token and R(S64) + cell bias of group token tid
     int doc, prev;  // documents of chunk embeddings tid and tid - 1 (-1 outside the chunk)
 };
 
-template <int NBITS>
-__global__ __launch_bounds__(kMxBlock, 3) void k_scan_mx(WaveArgs a) {
-    constexpr int BYTES = kDim * NBITS / 8;  // code bytes per embedding
-    constexpr int CW = NBITS;                // code words per lane: 32 dimensions of b bits
-    constexpr int NSLOT = 24;                // (plane, slice, lane group) slots of 16 bytes
+// LDS of the wide scan with token groups of G
+template <int NBITS, int G>
+struct MxShared {
+    static constexpr int NSLOT = 24;  // (plane, slice, lane group) slots of 16 bytes
     // row of the run table: the 16 token rows one atomic writes start 4 banks apart; column
     // kMxChunk takes the scores of embeddings past the chunk's end and is never read
-    constexpr int TPAD = kMxChunk + 4;
-    constexpr int NW = kMxBlock / 64;
-    constexpr int QPT = NSLOT * kMxGroup / kMxBlock;  // query slots staged per thread
-    constexpr int TPW = kMxChunk / (16 * NW);          // 16-embedding tiles per wave
-    // the run pass gives each thread at most one embedding of the chunk, the query staging
-    // splits evenly over the threads, and the waves split the tiles evenly
-    static_assert(kMxChunk <= kMxBlock, "one thread per chunk embedding");
-    static_assert(NSLOT * kMxGroup % kMxBlock == 0, "query staging");
-    static_assert(kMxChunk % (16 * NW) == 0, "tiles per wave");
+    static constexpr int TPAD = kMxChunk + 4;
     // query digit planes of the item's tokens, one padded row per token: the staging writes
     // of consecutive threads are contiguous, and the 16 tokens of an operand read lie 400 bytes apart
-    __shared__ v4i s_q[kMxGroup][NSLOT + 1];
-    __shared__ unsigned s_cterm[kMxGroup];   // R(S64) + the cell bias of each token (0 past the group)
-    __shared__ __attribute__((aligned(16))) int64_t s_row[2][kMxGroup];  // its token-max row offset
-    __shared__ unsigned s_tab[kMxGroup * TPAD];  // max score of (token, document run of the chunk)
-    __shared__ __attribute__((aligned(16))) int s_run[kMxChunk];  // run of each chunk embedding (kMxChunk past its end)
-    __shared__ int s_rdoc[kMxChunk];         // document of each run
-    __shared__ int s_rstart[kMxChunk];       // its first embedding in the chunk
-    __shared__ int s_wruns[NW];              // runs starting in each wave's quarter of the chunk
-    __shared__ unsigned s_claim;             // the batch thread 0 claimed
-    __shared__ unsigned s_wd[NBITS == 8 ? 256 : 1];  // b = 8: the three digits of Q(omega[v]) in bytes 0..2
+    v4i q[G][NSLOT + 1];
+    __attribute__((aligned(16))) int64_t row[2][G];  // the tokens' token-max row offsets
+    __attribute__((aligned(16))) int run[kMxChunk];  // run of each chunk embedding (kMxChunk past its end)
+    unsigned cterm[G];      // R(S64) + the cell bias of each token (0 past the group)
+    unsigned tab[G * TPAD];  // max score of (token, document run of the chunk)
+    int rdoc[kMxChunk];     // document of each run
+    int rstart[kMxChunk];   // its first embedding in the chunk
+    int wruns[kMxBlock / 64];  // runs starting in each wave's quarter of the chunk
+    unsigned claim;         // the batch thread 0 claimed
+    unsigned wd[NBITS == 8 ? 256 : 1];  // b = 8: the three digits of Q(omega[v]) in bytes 0..2
+};
+
+template <int NBITS, int G>
+__device__ __forceinline__ void scan_wide(const WaveArgs& a, MxShared<NBITS, G>& sm) {
+    constexpr int BYTES = kDim * NBITS / 8;  // code bytes per embedding
+    constexpr int CW = NBITS;                // code words per lane: 32 dimensions of b bits
+    constexpr int NSLOT = MxShared<NBITS, G>::NSLOT, TPAD = MxShared<NBITS, G>::TPAD;
+    constexpr int NW = kMxBlock / 64;
+    constexpr int QPT = (NSLOT * G + kMxBlock - 1) / kMxBlock;  // query slots staged per thread
+    constexpr int TPW = kMxChunk / (16 * NW);                   // 16-embedding tiles per wave
+    // the run pass gives each thread at most one embedding of the chunk, the groups are whole
+    // 16-token tiles, and the waves split the tiles evenly
+    static_assert(kMxChunk <= kMxBlock, "one thread per chunk embedding");
+    static_assert(G % 16 == 0, "token tiles");
+    static_assert(kMxChunk % (16 * NW) == 0, "tiles per wave");
+    auto& s_q = sm.q;
+    auto& s_cterm = sm.cterm;
+    auto& s_row = sm.row;
+    auto& s_tab = sm.tab;
+    auto& s_run = sm.run;
+    auto& s_rdoc = sm.rdoc;
+    auto& s_rstart = sm.rstart;
+    auto& s_wruns = sm.wruns;
+    auto& s_claim = sm.claim;
+    auto& s_wd = sm.wd;
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
@@ -431,7 +448,7 @@ __global__ __launch_bounds__(kMxBlock, 3) void k_scan_mx(WaveArgs a) {
     const uint8_t* __restrict__ codes = a.codes;
     const int32_t* __restrict__ doc_ids = a.doc_ids;
     unsigned* __restrict__ tokmax = a.tokmax;
-    for (int i = tid; i < kMxGroup * TPAD; i += kMxBlock) s_tab[i] = kTokAbsent;
+    for (int i = tid; i < G * TPAD; i += kMxBlock) s_tab[i] = kTokAbsent;
 
     // the software pipeline: while item i is scored, the query digits, bases and documents of
     // item i + 1 are in flight, its codes are loaded before item i's flush, and the wave
@@ -491,7 +508,7 @@ __global__ __launch_bounds__(kMxBlock, 3) void k_scan_mx(WaveArgs a) {
             rec = plan_load(reinterpret_cast<const v4i*>(a.list_rec), p);
             rec_item = plan_load(list_item, p);
         }
-        return mx_decode(rec, item, rec_item);
+        return mx_decode<G>(rec, item, rec_item);
     };
 
     request();
@@ -511,14 +528,14 @@ __global__ __launch_bounds__(kMxBlock, 3) void k_scan_mx(WaveArgs a) {
     // terms (score 0 = absent); the token-max row offsets alternate between two buffers, since
     // the previous item's flush still reads its own
     auto stage = [&](const MxItem& x, int par) {
-        if (tid < kMxGroup) {
+        if (tid < G) {
             s_cterm[tid] = tid < x.np ? (unsigned)st.base : 0u;  // R(S64) + the cell bias
             s_row[par][tid] = (int64_t)st.tok * a.n_docs;
         }
 #pragma unroll
         for (int i = 0; i < QPT; ++i) {
             const int k = tid + kMxBlock * i;
-            s_q[k / NSLOT][k % NSLOT] = st.q[i];
+            if (NSLOT * G % kMxBlock == 0 || k < NSLOT * G) s_q[k / NSLOT][k % NSLOT] = st.q[i];
         }
         if (tid == 0 && claimed) s_claim = claim;
     };
@@ -673,6 +690,13 @@ __global__ __launch_bounds__(kMxBlock, 3) void k_scan_mx(WaveArgs a) {
     }
 }
 
+// Waves of more than kMxSmallTokens tokens: a launch of the wide scan alone.
+template <int NBITS>
+__global__ __launch_bounds__(kMxBlock, 3) void k_scan_mx(WaveArgs a) {
+    __shared__ MxShared<NBITS, kMxGroup> sm;
+    scan_wide<NBITS, kMxGroup>(a, sm);
+}
+
 // Orders a wave's LDS writes before its later LDS reads by other lanes (one wave per table).
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
@@ -701,22 +725,30 @@ __device__ __forceinline__ void wave_lds_sync() {
 // flight, and the code words stream through DEPTH buffers (below). The query rows go through
 // LDS into the operand registers, which are free once a group's tiles are scored.
 template <int NBITS>
-__global__ __launch_bounds__(kMxBlock) void k_scan_narrow(WaveArgs a) {
+struct NrShared {
+    static constexpr int NW = kMxBlock / 64;
+    static constexpr int TPAD = kMxChunk + 4;
+    static constexpr int QSLOTS = kNrGroup * 24;  // 16-byte query digit slots of a group's tokens
+    v4i qrow[NW][QSLOTS];               // query digit rows of the next group's tokens
+    unsigned tab[NW][kNrGroup * TPAD];  // (token of the group, run) maxima
+    int run[NW][kMxChunk];              // run of each embedding of the chunk
+    int rdoc[NW][kMxChunk];             // document of each run
+    int rstart[NW][kMxChunk + 1];       // its first embedding; the chunk's length after the last
+    unsigned wd[NBITS == 8 ? 256 : 1];  // b = 8: the three digits of Q(omega[v]) in bytes 0..2
+};
+
+template <int NBITS>
+__device__ __forceinline__ void scan_narrow(const WaveArgs& a, NrShared<NBITS>& sm) {
     constexpr int BYTES = kDim * NBITS / 8;
-    constexpr int NW = kMxBlock / 64;
-    constexpr int NSLOT = 24;                   // 16-byte query digit slots of a token
-    constexpr int QSLOTS = kNrGroup * NSLOT;    // slots of a group's query rows
+    constexpr int NW = NrShared<NBITS>::NW;
+    constexpr int NSLOT = 24;  // 16-byte query digit slots of a token
+    constexpr int QSLOTS = NrShared<NBITS>::QSLOTS;
     constexpr int DEPTH = NBITS <= 4 ? 4 : 2;  // code-word buffers of the tile stream
-    constexpr int TPAD = kMxChunk + 4;
+    constexpr int TPAD = NrShared<NBITS>::TPAD;
     static_assert(kMxChunk % 64 == 0 && kMxChunk <= 4 * 64, "four rounds of the run pass");
     static_assert(kNrGroup == 3, "rows of a group's tile: four classes of three tokens, then their fifth");
     static_assert(QSLOTS > 64 && QSLOTS <= 128, "two query-row slots per lane");
-    __shared__ unsigned s_tab[NW][kNrGroup * TPAD];  // (token of the group, run) maxima
-    __shared__ int s_run[NW][kMxChunk];              // run of each embedding of the chunk
-    __shared__ int s_rdoc[NW][kMxChunk];             // document of each run
-    __shared__ int s_rstart[NW][kMxChunk + 1];       // its first embedding; the chunk's length after the last
-    __shared__ v4i s_qrow[NW][QSLOTS];               // query digit rows of the next group's tokens
-    __shared__ unsigned s_wd[NBITS == 8 ? 256 : 1];
+    auto& s_wd = sm.wd;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: the plan reads are scalar
@@ -727,11 +759,11 @@ __global__ __launch_bounds__(kMxBlock) void k_scan_narrow(WaveArgs a) {
     weight_tables<NBITS>(a.weights, tab, s_wd, tid);
     if (NBITS == 8) __syncthreads();  // the only workgroup barrier: s_wd is written
 
-    unsigned* stab = s_tab[wave];
-    int* runs = s_run[wave];
-    int* rdoc = s_rdoc[wave];
-    int* rstart = s_rstart[wave];
-    v4i* qrow = s_qrow[wave];
+    unsigned* stab = sm.tab[wave];
+    int* runs = sm.run[wave];
+    int* rdoc = sm.rdoc[wave];
+    int* rstart = sm.rstart[wave];
+    v4i* qrow = sm.qrow[wave];
     for (int i = lane; i < kNrGroup * TPAD; i += 64) stab[i] = kTokAbsent;
     const int64_t n_list = plan_load(a.list_n2, 0);
     const v4i* qdig = reinterpret_cast<const v4i*>(a.qdig);
@@ -978,6 +1010,33 @@ __global__ __launch_bounds__(kMxBlock) void k_scan_narrow(WaveArgs a) {
     }
 }
 
+template <int NBITS>
+__global__ __launch_bounds__(kMxBlock) void k_scan_narrow(WaveArgs a) {
+    __shared__ NrShared<NBITS> sm;
+    scan_narrow<NBITS>(a, sm);
+}
+
+// Waves of at most kMxSmallTokens tokens: both scans in one launch. Every workgroup first takes
+// its share of the narrow scan's chunks, then items of the wide scan from the batch counter, so
+// the workgroups that end their chunks early take more of the items, and there is one ramp and
+// one tail instead of two. Token groups of 16 (26 KB of LDS, and at b <= 2 127 VGPRs) put four
+// workgroups on a CU instead of three; a cluster that few tokens probe loses nothing by the
+// smaller groups, whereas in larger waves each group's repeated decode costs more.
+// One query of 32 tokens, two launches -> one: 1,024 clusters 87 -> 85 us, 6.3M embeddings (b = 4)
+// 181 -> 158 us, 70M (b = 2) 490 -> 452 us, 600M (b = 2) 3.13 -> 2.94 ms for the whole search. Groups of
+// 16 in larger waves: 48 queries at 600M 44.6 -> 48.3 ms, 256 at 70M 30.5 -> 34.6 ms. Workgroups of
+// eight waves (two to a CU, 121 VGPRs) lost in every wave: 3.01 -> 3.64 ms and 44.6 -> 50.4 ms.
+template <int NBITS>
+__global__ __launch_bounds__(kMxBlock, NBITS <= 2 ? 4 : 3) void k_scan_small(WaveArgs a) {
+    __shared__ union {
+        NrShared<NBITS> nr;
+        MxShared<NBITS, kMxGroupSmall> mx;
+    } sm;
+    scan_narrow<NBITS>(a, sm.nr);
+    __syncthreads();  // no wave reads the narrow scan's LDS any more
+    scan_wide<NBITS, kMxGroupSmall>(a, sm.mx);
+}
+
 void launch_wave_prep(const WaveArgs& a, uint32_t* ep, uint32_t last, hipStream_t s) {
     const int64_t n_tok = (int64_t)a.n_q * a.n_qtok;
     int64_t n0 = a.n_c > a.n_q ? a.n_c : a.n_q;
@@ -1015,6 +1074,16 @@ void launch_scan_narrow(const WaveArgs& a, int32_t grid, hipStream_t s) {
     }
 }
 
+void launch_scan_small(const WaveArgs& a, hipStream_t s) {
+    const dim3 g((unsigned)a.scan_grid), block(kMxBlock);
+    switch (a.nbits) {
+        case 1: hipLaunchKernelGGL(k_scan_small<1>, g, block, 0, s, a); break;
+        case 2: hipLaunchKernelGGL(k_scan_small<2>, g, block, 0, s, a); break;
+        case 4: hipLaunchKernelGGL(k_scan_small<4>, g, block, 0, s, a); break;
+        default: hipLaunchKernelGGL(k_scan_small<8>, g, block, 0, s, a); break;
+    }
+}
+
 int scan_narrow_blocks_per_cu(int nbits) {
     int n = 0;
     const void* k = nbits == 1   ? (const void*)k_scan_narrow<1>
@@ -1031,6 +1100,16 @@ int scan_mx_blocks_per_cu(int nbits) {
                     : nbits == 2 ? (const void*)k_scan_mx<2>
                     : nbits == 4 ? (const void*)k_scan_mx<4>
                                  : (const void*)k_scan_mx<8>;
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kMxBlock, 0);
+    return n > 0 ? n : 1;
+}
+
+int scan_small_blocks_per_cu(int nbits) {
+    int n = 0;
+    const void* k = nbits == 1   ? (const void*)k_scan_small<1>
+                    : nbits == 2 ? (const void*)k_scan_small<2>
+                    : nbits == 4 ? (const void*)k_scan_small<4>
+                                 : (const void*)k_scan_small<8>;
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kMxBlock, 0);
     return n > 0 ? n : 1;
 }

@@ -243,6 +243,22 @@ def test_wide_and_narrow_scans_agree(narrow_max, monkeypatch):
     run_both(data, label=f"narrow_max={narrow_max} tiny b=2 literal", literal=True)
 
 
+@pytest.mark.parametrize("nbits", [1, 2, 4, 8])
+@pytest.mark.parametrize("narrow_max", ["0", "3", "4096"], ids=["all-wide", "narrow3", "all-narrow"])
+def test_small_waves_scan_in_one_launch(nbits, narrow_max, monkeypatch):
+    """Waves of at most 32 tokens run both scans in one launch, with token groups of 16; larger
+    waves run them apart, in groups of 32. At one token, at the edges of a group (16, 17), at
+    the last small wave (32 tokens, as one query or as two) and at the first larger one (33), with
+    clusters probed by most tokens of the wave, every split gives the oracle's results."""
+    monkeypatch.setenv("WARP_NARROW_MAX", narrow_max)
+    for nq, nt in ((1, 1), (1, 16), (1, 17), (2, 16), (1, 32), (3, 11)):
+        wl = synth.random_small_workload(60 + nt, n_centroids=40, n_docs=300, max_len=30, nbits=nbits,
+                                         n_queries=nq, n_qtok=nt, nprobe=24, t_prime=200, k=30)
+        data = synth.make_index(wl, workers=1)
+        run_both(data, label=f"narrow_max={narrow_max} b={nbits} {nq}x{nt}")
+        run_both(data, label=f"narrow_max={narrow_max} b={nbits} {nq}x{nt} literal", literal=True)
+
+
 def test_empty_clusters_and_ragged_tiles():
     # many centroids, few embeddings: most clusters are empty; tails of every tile are ragged
     wl = synth.random_small_workload(11, n_centroids=1024, n_docs=700, max_len=9, nbits=4, n_queries=6,
