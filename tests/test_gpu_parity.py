@@ -259,6 +259,17 @@ def test_small_waves_scan_in_one_launch(nbits, narrow_max, monkeypatch):
         run_both(data, label=f"narrow_max={narrow_max} b={nbits} {nq}x{nt} literal", literal=True)
 
 
+@pytest.mark.parametrize("n_c", [1, 5, 16, 17, 66, 1030])
+def test_filter_of_few_tokens(n_c):
+    """Waves of at most 32 tokens score the centroids 16 at a time with the tokens in registers: at one
+    centroid, at the edges of a tile of 16, with rows of bins that are no multiple of four, and at the
+    edges of the token tiles, the probed centroids and m_i are the oracle's."""
+    for nq, nt in ((1, 1), (1, 16), (1, 17), (1, 32), (2, 15)):
+        wl = synth.random_small_workload(80 + nt, n_centroids=n_c, n_docs=200, max_len=12, nbits=2, n_queries=nq,
+                                         n_qtok=nt, nprobe=min(n_c, 12), t_prime=60, k=15)
+        run_both(synth.make_index(wl, workers=1), label=f"n_c={n_c} {nq}x{nt}")
+
+
 def test_empty_clusters_and_ragged_tiles():
     # many centroids, few embeddings: most clusters are empty; tails of every tile are ragged
     wl = synth.random_small_workload(11, n_centroids=1024, n_docs=700, max_len=9, nbits=4, n_queries=6,
