@@ -289,6 +289,14 @@ def test_cluster_offsets_over_several_passes():
     run_both(data, label="70001 clusters")
 
 
+@pytest.mark.parametrize("n_c", [524288, 524289])
+def test_plan_block_sums_on_both_sides_of_the_limit(n_c):
+    # 64 blocks of clusters: the emit kernel sums the block totals itself; 65: k_plan_prefix does
+    wl = synth.random_small_workload(13, n_centroids=n_c, n_docs=3000, max_len=24, nbits=1, n_queries=2,
+                                     n_qtok=5, nprobe=64, t_prime=50, k=20)
+    run_both(synth.make_index(wl, workers=1), label=f"{n_c} clusters")
+
+
 # ----------------------------------------------------------------------------- workloads
 
 def test_tiny_workload_exact_and_real_valued():
