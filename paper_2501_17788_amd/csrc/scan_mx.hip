@@ -116,6 +116,16 @@ __device__ __forceinline__ void weight_tables(const float* weights, unsigned (&t
     }
 }
 
+// Selector of a nibble's half of its table, bytes 4 .. 7 (of the upper eight entries) where bit 2 of
+// the byte is set, else 0 .. 3. The mask sits in a vector register, so that this is one v_and_or_b32.
+// (101 instead of 108 VALU instructions per b = 4 tile: 256 queries at 6.3M embeddings 4.41 -> 4.35 ms, one
+// query 154.5 -> 152.8 us, 64 queries at 240M 60.4 -> 59.9 ms.)
+__device__ __forceinline__ unsigned nibble_pick(unsigned x) {
+    unsigned mask = 0x04040404u;
+    asm("" : "+v"(mask));
+    return (x & mask) | 0x03020100u;
+}
+
 // The three weight-digit planes of one lane's 32 dimensions of a 16-embedding tile, in
 // operand order: W[p][s] is digit plane p of K slice s (slot_of_dim). `wj` holds the
 // lane's code words of the tile: v_perm_b32 lookups in the register tables (3 per four
@@ -130,9 +140,8 @@ __device__ __forceinline__ void decode_weight_digits(const unsigned (&wj)[NBITS]
         for (int m = 0; m < 4; ++m) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const unsigned x = h == 0 ? (wj[m % CW] >> 4) & 0x0F0F0F0Fu : wj[m % CW] & 0x0F0F0F0Fu;
-                const unsigned x7 = x & 0x07070707u;
-                const unsigned pick = ((x >> 1) & 0x04040404u) | 0x03020100u;
+                const unsigned x7 = (h == 0 ? wj[m % CW] >> 4 : wj[m % CW]) & 0x07070707u;
+                const unsigned pick = nibble_pick(wj[m % CW] >> (h == 0 ? 5 : 1));
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
                     const unsigned lo8 = __builtin_amdgcn_perm(tab[p][1], tab[p][0], x7);
@@ -187,9 +196,8 @@ __device__ __forceinline__ v4i weight_operand(const unsigned (&wj)[NBITS], const
             const int m = 2 * s + mm;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const unsigned x = h == 0 ? (wj[m % NBITS] >> 4) & 0x0F0F0F0Fu : wj[m % NBITS] & 0x0F0F0F0Fu;
-                const unsigned x7 = x & 0x07070707u;
-                const unsigned pick = ((x >> 1) & 0x04040404u) | 0x03020100u;
+                const unsigned x7 = (h == 0 ? wj[m % NBITS] >> 4 : wj[m % NBITS]) & 0x07070707u;
+                const unsigned pick = nibble_pick(wj[m % NBITS] >> (h == 0 ? 5 : 1));
                 const unsigned lo8 = __builtin_amdgcn_perm(tab[p][1], tab[p][0], x7);
                 const unsigned hi8 = __builtin_amdgcn_perm(tab[p][3], tab[p][2], x7);
                 w[2 * mm + h] = (int)__builtin_amdgcn_perm(hi8, lo8, pick);
