@@ -337,8 +337,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
     // from step 4 on, hist holds the sizes of the rescored centroids
     int* const szA = reinterpret_cast<int*>(hist);
     int* const szB = szA + kSelCap;
-    // and the selected centroids and their fixed-point scores by rank (scores that are not numbers,
-    // of a token that the norm check refuses, leave ranks empty: no centroid)
+    // and the selected centroids and their fixed-point scores by rank. Scores that are not numbers,
+    // of a token that the norm check refuses, share ranks and leave others empty (-1: no centroid);
+    // only the centroids that stand in s_sel are counted, so that the plan's buckets are filled whole
     int* const s_sel = szB + kSelCap;
     int* const s_base = s_sel + kSelCap;
     static_assert(4 * kSelCap * sizeof(int) <= sizeof(hist), "must fit the histogram's LDS");
@@ -457,7 +458,6 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
         if (r < P) {
             const int c = idA[p];
             s_sel[r] = c;
-            atomicAdd(&a.ccount[c], 1);
             s_base[r] = (int32_t)to_fixed(sA[p]);
             cum[r] = szA[p];
         }
@@ -465,6 +465,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
     __syncthreads();
     for (int j = tid; j < P; j += NT) {
         sel[j] = s_sel[j];
+        if (s_sel[j] >= 0) atomicAdd(&a.ccount[s_sel[j]], 1);
         base[j] = s_base[j];
         if (a.dbg_sel) a.dbg_sel[(int64_t)t * P + j] = s_sel[j];
     }
@@ -620,13 +621,13 @@ __global__ __launch_bounds__(kSelThreads) void k_select_rest(WaveArgs a) {
     rank_all(sA, idA, P, [&](int p, int r) {
         const int c = idA[p];
         s_sel[r] = c;
-        atomicAdd(&a.ccount[c], 1);
         s_base[r] = (int32_t)to_fixed(sA[p]);
         cum[r] = a.sizes[c];
     });
     __syncthreads();
     for (int j = tid; j < P; j += NT) {
         sel[j] = s_sel[j];
+        if (s_sel[j] >= 0) atomicAdd(&a.ccount[s_sel[j]], 1);
         base[j] = s_base[j];
         if (a.dbg_sel) a.dbg_sel[(int64_t)t * P + j] = s_sel[j];
     }

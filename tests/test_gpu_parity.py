@@ -500,6 +500,36 @@ def test_async_query_norm_error_reported_by_sync():
     compare(got, oracle.search_index(data, nprobe=4, t_prime=10, k=5), label="after a norm error")
 
 
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), 1e30], ids=["nan", "inf", "1e30"])
+@pytest.mark.parametrize("n_c,nprobe", [(600, 20), (600, 300), (3000, 20), (3000, 300), (700, 600)])
+def test_unusable_query_token_is_refused_and_harmless(n_c, nprobe, value):
+    """The asynchronous searches check query tokens on the device, beside the search: scores that are
+    not numbers take no ranks, so the selection must count exactly the centroids that it lists (the
+    plan reads as many pairs as are counted). The error comes at sync, the next search is right."""
+    import torch
+
+    w = _engine()
+    data = synth.make_index(synth.random_small_workload(90, n_centroids=n_c, n_docs=900, max_len=12, nbits=4,
+                                                        n_queries=4, n_qtok=8, nprobe=nprobe, t_prime=300, k=20),
+                            workers=1)
+    bad = data.queries.copy()
+    bad[1, 2] = value
+    bad[2, 5, 7] = value
+    want = oracle.search_index(data)
+    with w.Index.from_synthetic(data) as ix:
+        for name in ("search_async", "search_noalloc"):
+            say(f"[unusable token] {name} n_c={n_c} nprobe={nprobe} value={value}")
+            search = getattr(ix, name)
+            search(torch.from_numpy(bad).cuda(), nprobe, 300, 20)
+            with pytest.raises(w.WarpError) as e:
+                ix.sync()
+            assert e.value.code == w.EINVAL and "norm" in e.value.msg
+            ids, scores, counts, fixed = search(torch.from_numpy(data.queries).cuda(), nprobe, 300, 20)
+            ix.sync()
+            for got, key in ((ids, "ids"), (scores, "scores"), (counts, "counts"), (fixed, "fixed")):
+                np.testing.assert_array_equal(got.cpu().numpy(), want[key], err_msg=f"{name}: {key}")
+
+
 # ----------------------------------------------------------------------------- the 256-query workload
 
 @pytest.fixture(scope="module")
