@@ -252,7 +252,10 @@ int warp_centroid_filter_scores(warp_index* idx, const float* queries, int32_t n
 /*
  * Index construction on the device (Section 4.1): k-means on a sample of the
  * token embeddings, then every token encoded as a b-bit quantised residual to
- * its nearest centroid. Every pointer is device memory; the call blocks.
+ * its nearest centroid. Every pointer is device memory; the call blocks. It
+ * starts after the work that is on the null stream, and on the streams that
+ * synchronise with it, when it is called; inputs made on a non-blocking stream
+ * must be complete.
  *
  *   tokens           [n_tokens][128] fp32, finite, norm <= 1 + 1e-3
  *   token_docs       [n_tokens] document id of each token, in [0, n_docs)

@@ -1178,6 +1178,9 @@ int warp_build_index(const float* tokens, const int32_t* token_docs, int64_t n_t
     int rc = check_device();
     if (rc) return rc;
     const int64_t n_c = n_centroids;
+    // the build's stream waits for no other: the caller's work on the null stream (and on the
+    // streams that synchronise with it) ends before the inputs are read
+    HIP_TRY(hipStreamSynchronize(nullptr));
     hipStream_t s = nullptr;
     HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
     const int64_t N = n_tokens;

@@ -142,6 +142,42 @@ def test_build_errors():
         w.build_index(Xt, Dt, len(lens), C0, sample, 1, 3, 10)
 
 
+def test_build_starts_after_the_null_stream():
+    """The C entry point reads its inputs after the work that is on the null stream: the inputs are
+    copied into place behind a few tens of milliseconds of other work, with no synchronisation
+    before the call. (What the buffers hold before are other inputs, usable as well.)"""
+    import ctypes
+
+    import torch
+
+    import paper_2501_17788_amd as w
+
+    data, X, docs, lens = _inputs(43, n_docs=300, max_len=20, n_c=32)
+    sample = w.sample_passages(lens, c=6.0, seed=1)
+    C0 = w.initial_centroids(X, sample, 32, seed=2)
+    want = oracle.build_index(X, docs, C0, sample, 2, 4, 500)
+    assert torch.cuda.current_stream().cuda_stream == 0
+    new = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (X, docs, C0, sample)]
+    x, d, c0, s = (a.flip(0).contiguous() for a in new)
+    n, n_c = len(X), len(C0)
+    outs = [torch.empty(shape, dtype=dt, device="cuda") for shape, dt in
+            (((n_c, 128), torch.float32), ((n_c + 1,), torch.int64), ((n,), torch.int32), ((n, 64), torch.uint8),
+             ((16,), torch.float32), ((15,), torch.float32), ((n,), torch.int32))]
+    big = torch.ones((8192, 8192), device="cuda")
+    torch.cuda.synchronize()
+    say("[build behind other work]")
+    for _ in range(4):
+        torch.mm(big, big)
+    for dst, src in zip((x, d, c0, s), new):
+        dst.copy_(src)
+    P = ctypes.c_void_p
+    rc = w.lib.warp_build_index(P(x.data_ptr()), P(d.data_ptr()), n, len(lens), P(c0.data_ptr()), n_c, P(s.data_ptr()),
+                                len(sample), 2, 4, 500, *(P(o.data_ptr()) for o in outs))
+    assert rc == 0, w.last_error()
+    for o, key in zip(outs, ("centroids", "offsets", "doc_ids", "codes", "weights", "cutoffs", "assign")):
+        np.testing.assert_array_equal(o.cpu().numpy(), want[key], err_msg=key)
+
+
 def test_search_over_device_built_index():
     import torch
 
