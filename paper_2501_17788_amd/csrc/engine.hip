@@ -1238,20 +1238,18 @@ int warp_build_index(const float* tokens, const int32_t* token_docs, int64_t n_t
     int32_t* assign = assignment ? assignment : w.assign;
 
     // inputs: usable starting vectors, sample ids in range, finite tokens of norm <= 1 + 1e-3,
-    // document ids in range; the starting centroids are normalised where they will stay
+    // document ids in range. The starting vectors are checked in a copy (where the sums will
+    // stand): a refused call leaves the caller's outputs alone, and the two arrays may overlap.
     auto try_hip = [&](hipError_t e, const char* what) {
         return e == hipSuccess ? WARP_OK : fail(WARP_EDEVICE, "%s failed: %s", what, hipGetErrorString(e));
     };
     launch_fill_i32(err, 1, 0, s);
     launch_fill_i32((int32_t*)w.first, 4, -1, s);
-    // (by way of the scratch: the two arrays may overlap)
-    rc = try_hip(hipMemcpyAsync(w.sums, init_centroids, (size_t)n_c * kDim * 4, hipMemcpyDefault, s),
+    float* start = (float*)w.sums;
+    rc = try_hip(hipMemcpyAsync(start, init_centroids, (size_t)n_c * kDim * 4, hipMemcpyDefault, s),
                  "copying the starting vectors");
-    if (!rc)
-        rc = try_hip(hipMemcpyAsync(centroids, w.sums, (size_t)n_c * kDim * 4, hipMemcpyDeviceToDevice, s),
-                     "copying the starting vectors");
     if (rc) return done(rc);
-    launch_check_build(centroids, n_centroids, sample_ids, n_sample, N, w.first, s);
+    launch_check_build(start, n_centroids, sample_ids, n_sample, N, w.first, s);
     launch_check_queries(tokens, N, err, s);
     launch_check_docs(token_docs, N, n_docs, err, s);
     int32_t herr = 0;
@@ -1270,6 +1268,9 @@ int warp_build_index(const float* tokens, const int32_t* token_docs, int64_t n_t
     if (herr & kErrQueryNorm) return done(fail(WARP_EINVAL, "a token is not finite or has norm > 1 + 1e-3"));
     if (herr & kErrDocRange) return done(fail(WARP_EINVAL, "a token's document id is outside [0, n_docs)"));
 
+    rc = try_hip(hipMemcpyAsync(centroids, start, (size_t)n_c * kDim * 4, hipMemcpyDeviceToDevice, s),
+                 "copying the starting vectors");
+    if (rc) return done(rc);
     launch_normalize_rows(centroids, n_centroids, s);  // the starting centroids
     auto assign_rows = [&](const float* x, int64_t n, int32_t* out) {
         launch_assign(x, n, centroids, n_centroids, w.match, out, err, s);

@@ -178,6 +178,39 @@ def test_build_starts_after_the_null_stream():
         np.testing.assert_array_equal(o.cpu().numpy(), want[key], err_msg=key)
 
 
+def test_refused_build_leaves_the_outputs_alone():
+    """Every refusal of an input comes before the first output is written, also with the starting
+    vectors in the buffer of the centroids."""
+    import ctypes
+
+    import torch
+
+    import paper_2501_17788_amd as w
+
+    data, X, docs, lens = _inputs(41, n_docs=50, max_len=6, n_c=16)
+    sample = w.sample_passages(lens, c=5.0, seed=1)
+    C0 = w.initial_centroids(X, sample, 16, seed=2)
+    zero, nan, out_of_range = C0.copy(), C0.copy(), sample.copy()
+    zero[2], nan[3, 4], out_of_range[0] = 0, np.nan, len(X)
+    n, P = len(X), ctypes.c_void_p
+    for label, x, n_docs, c0, s in (("zero", X, len(lens), zero, sample), ("not finite", X, len(lens), nan, sample),
+                                    ("sample id", X, len(lens), C0, out_of_range), ("norm", X * 1.5, len(lens), C0, sample),
+                                    ("document id", X, len(lens) - 1, C0, sample)):
+        for overlap in (False, True):
+            say(f"[refused build] {label} overlap={overlap}")
+            xt, dt, ct, st = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (x, docs, c0, s))
+            cen = ct if overlap else torch.full_like(ct, 7.0)
+            outs = [cen] + [torch.full(shape, 7, dtype=t, device="cuda") for shape, t in
+                            (((17,), torch.int64), ((n,), torch.int32), ((n, 64), torch.uint8), ((16,), torch.float32),
+                             ((15,), torch.float32), ((n,), torch.int32))]
+            before = [o.clone() for o in outs]
+            rc = w.lib.warp_build_index(P(xt.data_ptr()), P(dt.data_ptr()), n, n_docs, P(ct.data_ptr()), 16,
+                                        P(st.data_ptr()), len(s), 1, 4, 10, *(P(o.data_ptr()) for o in outs))
+            assert rc == w.EINVAL and label in w.last_error()
+            for o, b in zip(outs, before):
+                np.testing.assert_array_equal(o.cpu().numpy(), b.cpu().numpy(), err_msg=label)
+
+
 def test_search_over_device_built_index():
     import torch
 
