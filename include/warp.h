@@ -175,11 +175,11 @@ int warp_index_info(const warp_index* idx, int32_t* n_centroids, int64_t* n_embe
  *   out_counts   [n_queries] host or NULL: min(k, number of candidate documents)
  *
  * Only candidate documents (those with at least one retrieved embedding) are
- * ranked. Blocks until the results are in host memory. If more than 1024
- * centroids of a token fall within about 3e-3 of a selection boundary (only
- * possible with degenerate centroid sets), the search is run again with the
- * selection that sorts every score, which gives the same results without that
- * limit.
+ * ranked. Blocks until the results are in host memory. If nprobe is at most 256
+ * and more than 1024 centroids of a token fall within about 3e-3 of a selection
+ * boundary (centroids that coincide, or t_prime in the middle of the scores of
+ * some 44,000 centroids and more), the search is run again with the selection
+ * that sorts every score, which gives the same results without that limit.
  */
 int warp_search(warp_index* idx, const float* queries, int32_t n_queries, int32_t n_qtok,
                 int32_t nprobe, int64_t t_prime, int32_t k, int32_t* out_doc_ids,
@@ -190,11 +190,12 @@ int warp_search(warp_index* idx, const float* queries, int32_t n_queries, int32_
  * (a hipStream_t, NULL for the default stream); returns once the work is
  * enqueued. out_fixed_scores [n_queries][k] (int64, INT64_MIN padding) and
  * out_counts may be NULL. Query norms are checked on the device: that error,
- * and a centroid-selection overflow (more than 1024 centroids whose scores fall
- * within about 3e-3 of a selection boundary, only possible with degenerate
- * centroid sets: WARP_ENOTSUP; warp_search and warp_search_debug retry such a
- * search with the sorting selection), are reported by warp_index_sync. The index's scratch memory
- * is shared by its searches: enqueue the searches of one index on one stream.
+ * and a centroid-selection overflow (nprobe at most 256 and more than 1024
+ * centroids whose scores fall within about 3e-3 of a selection boundary, as in
+ * warp_search: WARP_ENOTSUP; warp_search and warp_search_debug retry such a
+ * search with the sorting selection, and nprobe above 256 has no such limit),
+ * are reported by warp_index_sync. The index's scratch memory is shared by its
+ * searches: enqueue the searches of one index on one stream.
  */
 int warp_search_async(warp_index* idx, const float* queries, int32_t n_queries, int32_t n_qtok,
                       int32_t nprobe, int64_t t_prime, int32_t k, int32_t* out_doc_ids,

@@ -59,9 +59,9 @@ __device__ __forceinline__ void rank_all(const double* s, const int* id, int n, 
 // 32 part .. 32 part + 31 (one round trip for the whole row), and the running sum passes
 // from lane to lane in that order. Every lane of the four returns the score; the cluster's
 // size is loaded with the row.
-// (one copy per calling kernel: with one copy called from both selection kernels, each took
+// (one copy per calling kernel K: with one copy called from two selection kernels, each took
 // 97 VGPRs instead of 68)
-template <bool K>
+template <int K>
 __device__ __noinline__ double score64_quad(const float* __restrict__ cen, const int32_t* __restrict__ sizes,
                                                int c, const float* qs, int part, int& size) {
     const float4* row = reinterpret_cast<const float4*>(cen + (int64_t)c * kDim) + 8 * part;
@@ -499,140 +499,278 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
     }
 }
 
-// Selection of the tokens that k_select left (sel[0] = -2: a band of more than kSelCap centroids,
-// only with degenerate centroid sets), for P <= kSelCap: one workgroup per token over all its fp64
-// scores, recomputed in every pass. An MSB-first radix select over the order-reversing 64-bit score
-// keys, then over the ids among equal scores, finds the P-th centroid in (score desc, id asc)
-// order; another, over the sizes, the key of the first centroid whose inclusive size sum exceeds
-// t' (the highest key where the total does not). The P first are gathered and ranked. (Other tokens' workgroups exit at once.)
+// Ascending order of these keys is descending order of the scores (S64 is never -0.0).
+__device__ __forceinline__ unsigned long long score_key(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    return ~((b >> 63) ? ~b : (b | (1ull << 63)));
+}
+__device__ __forceinline__ double key_score(unsigned long long k) {
+    const unsigned long long b = ~k;
+    return __longlong_as_double((long long)((b >> 63) ? (b & ~(1ull << 63)) : ~b));
+}
+
+// Where the running weight of (value, weight) entries, values ascending, first exceeds a limit.
+struct Crossing {
+    unsigned long long lo, hi;  // the value lies in [lo, hi] (the largest value if none exceeds the limit)
+    unsigned long long before;  // weight of every entry below lo
+    unsigned n;                 // entries in [lo, hi]
+};
+// for_each(f) calls f(value, weight) for every entry, the same ones each time, spread over the
+// block. Rounds of a minimum and maximum, then a histogram of kSelThreads bins between them, until
+// the range holds at most `stop` entries or one value. hist: kSelThreads words; every thread calls it.
+template <typename F>
+__device__ __forceinline__ Crossing find_crossing(F for_each, unsigned long long limit, unsigned stop,
+                                                  unsigned long long* hist, unsigned long long* wtot) {
+    constexpr int NW = kSelThreads / 64;
+    __shared__ unsigned long long s_mn[NW], s_mx[NW], s_before;
+    __shared__ unsigned s_cnt[NW];
+    __shared__ int s_bin;
+    const int tid = threadIdx.x;
+    Crossing x{0, ~0ull, 0, 0};
+    for (;;) {
+        unsigned long long mn = ~0ull, mx = 0;
+        unsigned n = 0;
+        for_each([&](unsigned long long v, unsigned long long) {
+            if (v < x.lo || v > x.hi) return;
+            mn = v < mn ? v : mn;
+            mx = v > mx ? v : mx;
+            ++n;
+        });
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const unsigned long long a = __shfl_xor(mn, off, 64), b = __shfl_xor(mx, off, 64);
+            mn = a < mn ? a : mn;
+            mx = b > mx ? b : mx;
+            n += __shfl_xor(n, off, 64);
+        }
+        if ((tid & 63) == 0) {
+            s_mn[tid >> 6] = mn;
+            s_mx[tid >> 6] = mx;
+            s_cnt[tid >> 6] = n;
+        }
+        hist[tid] = 0;
+        if (tid == 0) s_bin = -1;
+        __syncthreads();
+        n = 0;
+        for (int w = 0; w < NW; ++w) {
+            mn = s_mn[w] < mn ? s_mn[w] : mn;
+            mx = s_mx[w] > mx ? s_mx[w] : mx;
+            n += s_cnt[w];
+        }
+        x.lo = mn;
+        x.hi = mx;
+        x.n = n;
+        if (n <= stop || mn >= mx) break;  // uniform
+        int shift = 0;
+        while (((mx - mn) >> shift) >= (unsigned long long)kSelThreads) ++shift;
+        for_each([&](unsigned long long v, unsigned long long w) {
+            if (v >= mn && v <= mx) atomicAdd(&hist[(v - mn) >> shift], w);
+        });
+        __syncthreads();
+        unsigned long long total;
+        const unsigned long long own = hist[tid], incl = block_scan(own, wtot, &total);
+        if (x.before + incl > limit && x.before + incl - own <= limit) {
+            s_bin = tid;
+            s_before = x.before + incl - own;
+        }
+        __syncthreads();
+        if (s_bin < 0) {  // (only in the first round)
+            x.before += total;
+            x.lo = x.hi = mx;
+            break;
+        }
+        x.lo = mn + ((unsigned long long)s_bin << shift);
+        x.hi = x.lo + ((1ull << shift) - 1);
+        x.before = s_before;
+        __syncthreads();
+    }
+    __syncthreads();
+    return x;
+}
+
+constexpr int kRestCap = 10240;  // (score, centroid) entries held in LDS
+constexpr int kRestTile = 4096;  // centroids looked at together where a band holds more (their list
+                                 // takes the end of the entries' LDS)
+
+// Selection of the tokens that k_select left (sel[0] = -2: a band of more than kSelCap centroids),
+// for P <= kSelThreads: one workgroup per token (the others' exit at once) over the same two bands,
+// which need not be small here: the five bins around the t' crossing hold 4% of the centroids where
+// t' lies in the middle of normally spread scores, 5,200 of 2^17. A band of at most kRestCap
+// centroids is scored once, into LDS; a larger one (half a million centroids, or many that
+// coincide) is scored again in each of the few rounds that narrow it to what fits. The P first
+// are ranked as in k_select.
+// Bound by the rows of the bands, 512 bytes each, four lanes per row. Whole searches, nprobe 400, t' in
+// the middle: one query at 2^17 centroids 0.36 ms and 64 queries 2.8 ms (sorting every score: 1.5 and
+// 86 ms; scoring every centroid in each round: 21 and 203 ms), at 2^18 0.49 and 4.5 ms (3.2 and 181 ms by
+// sorting); 2,000 of 3,000 centroids equal, three queries: 0.31 ms (0.41 by sorting). Slower than sorting
+// only for a few queries with more than kRestCap coinciding centroids: 12,000 of 2^15 and one query, 1.13
+// against 0.55 ms (eight queries: 2.50 against 2.49).
 __global__ __launch_bounds__(kSelThreads) void k_select_rest(WaveArgs a) {
     constexpr int NT = kSelThreads;
-    __shared__ unsigned long long hist[256], whist[256];
+    constexpr int kGather = kRestCap - kRestTile;  // entries gathered from a larger band
+    __shared__ unsigned long long hist[kSelBins];
     __shared__ unsigned long long wtot[NT / 64];
+    __shared__ unsigned long long s_key[kRestCap];
+    __shared__ int s_id[kRestCap];
     __shared__ float qs[kDim];
-    __shared__ double sA[kSelCap];
-    __shared__ int idA[kSelCap];
-    __shared__ int64_t cum[kSelCap];
-    __shared__ unsigned long long s_pre, s_wpre, s_need, s_wabove;
-    __shared__ int s_n;
+    __shared__ int s_n, s_tile, s_eq;
+    // the P first, by arrival and by rank
+    double* const sA = reinterpret_cast<double*>(hist);
+    int64_t* const cum = reinterpret_cast<int64_t*>(sA + NT);
+    int* const idA = reinterpret_cast<int*>(cum + NT);
+    int* const s_sel = idA + NT;
+    int* const s_base = s_sel + NT;
+    static_assert(NT * (2 * 8 + 3 * 4) <= sizeof(hist), "must fit the histogram's LDS");
+    static_assert(kBandProbe <= NT && kGather >= kRestTile + 2 * kBandProbe, "entries of a larger band");
+    int* const tile_ids = s_id + kGather;
     const int t = blockIdx.x, tid = threadIdx.x;
     const int n_c = a.n_c, P = a.nprobe;
     int32_t* sel = a.sel + (int64_t)t * P;
     if (sel[0] != -2) return;  // uniform
     const unsigned long long tp = (unsigned long long)a.t_prime;
+    const uint16_t* bins = a.filter_bins + (int64_t)t * n_c;
+    const int32_t* sizes = a.sizes;
+    for (int i = tid; i < kSelBins; i += NT) hist[i] = 0;
     if (tid < kDim) qs[tid] = a.queries[(int64_t)t * kDim + tid];
     __syncthreads();
-    auto score = [&](int c) {
-        const float* row = a.centroids + (int64_t)c * kDim;
-        double v = 0.0;
-        for (int d = 0; d < kDim; ++d) v = __builtin_fma((double)row[d], (double)qs[d], v);  // exact products
-        return v;
-    };
-    // ascending order of the keys is descending order of the scores
-    auto key_of = [](double x) {
-        unsigned long long b = (unsigned long long)__double_as_longlong(x);
-        b = (b >> 63) ? ~b : (b | (1ull << 63));
-        return ~b;
-    };
-    if (tid == 0) {
-        s_pre = 0;
-        s_wpre = 0;
-        s_need = (unsigned long long)P;
-        s_wabove = 0;
-        s_n = 0;
-    }
+    for_each_bin(bins, n_c, [&](int c, int b) { atomicAdd(&hist[b], kCntOne | (unsigned long long)sizes[c]); });
     __syncthreads();
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        for (int i = tid; i < 256; i += NT) {
-            hist[i] = 0;
-            whist[i] = 0;
-        }
-        __syncthreads();
-        const unsigned long long pre = s_pre, wpre = s_wpre;
-        const unsigned long long mask = shift == 56 ? 0 : ~0ull << (shift + 8);
-        for (int c = tid; c < n_c; c += NT) {
-            const unsigned long long k = key_of(score(c));
-            if ((k & mask) == pre) atomicAdd(&hist[(k >> shift) & 255], 1ull);
-            // (the count beside the size: an empty cluster may hold the highest key)
-            if ((k & mask) == wpre) atomicAdd(&whist[(k >> shift) & 255], kCntOne | (unsigned long long)a.sizes[c]);
-        }
-        __syncthreads();
-        if (tid == 0) {
-            unsigned long long run = 0;
-            int d = 0;
-            while (run + hist[d] < s_need) run += hist[d++];
-            s_need -= run;
-            s_pre = pre | ((unsigned long long)d << shift);
-            unsigned long long w = s_wabove;
-            int e = -1, last = 0;
-            for (int i = 0; i < 256; ++i) {
-                if (whist[i]) last = i;
-                if (e < 0 && w + (whist[i] & kSizeMask) > tp) e = i;
-                if (e < 0) w += whist[i] & kSizeMask;
+    const SelBounds bd = hist_bounds(hist, wtot, (uint32_t)P, tp);
+    const SelBand band = sel_band(bd.bP, bd.bt, bd.blo);
+    unsigned long long above = bd.wabove;  // size of every bin above the t' band
+    if (!band.clamp)
+        for (int b = bd.bt + 1; b <= band.hi; ++b) above -= hist[b] & kSizeMask;
+    unsigned long long nband[2] = {0, 0};  // centroids of the two bands
+    for (int b = tid; b < kSelBins; b += NT) {
+        nband[0] += b >= band.bA ? hist[b] >> 40 : 0;
+        nband[1] += b >= band.lo && b <= band.hi ? hist[b] >> 40 : 0;
+    }
+    for (int l = 0; l < 2; ++l) {
+        unsigned long long total;
+        (void)block_scan(nband[l], wtot, &total);
+        nband[l] = total;
+    }
+
+    for (int l = 0; l < 2; ++l) {  // the n_probe best, then m_i
+        const int b0 = l == 0 ? band.bA : band.lo, b1 = l == 0 ? kSelBins - 1 : band.hi;
+        const bool held = nband[l] <= (unsigned long long)kRestCap;  // uniform
+        // scores of ids[0 .. n): f(p, key), once per entry
+        auto score_list = [&](const int* ids, int n, auto&& f) {
+            for (int p = tid >> 2; p < n; p += NT / 4) {  // uniform over each four lanes
+                int sz;
+                const double v = score64_quad<2>(a.centroids, sizes, ids[p], qs, tid & 3, sz);
+                if ((tid & 3) == 0) f(p, score_key(v));
             }
-            if (e >= 0) s_wabove = w;
-            s_wpre = wpre | ((unsigned long long)(e >= 0 ? e : last) << shift);
-        }
-        __syncthreads();
-    }
-    // ids among the centroids of the P-th key: the s_need lowest
-    unsigned ipre = 0;
-    const unsigned long long kth = s_pre;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        for (int i = tid; i < 256; i += NT) hist[i] = 0;
-        __syncthreads();
-        const unsigned imask = shift == 24 ? 0u : ~0u << (shift + 8);
-        for (int c = tid; c < n_c; c += NT)
-            if (((unsigned)c & imask) == ipre && key_of(score(c)) == kth) atomicAdd(&hist[((unsigned)c >> shift) & 255], 1ull);
-        __syncthreads();
+        };
+        // every centroid of a larger band, ids ascending from tile to tile: f(key, centroid); g() at
+        // the start of each tile
+        auto for_band = [&](auto&& f, auto&& g) {
+            for (int c0 = 0; c0 < n_c; c0 += kRestTile) {  // uniform
+                if (tid == 0) s_tile = 0;
+                __syncthreads();
+                g();
+                for (int c = c0 + tid; c < c0 + kRestTile && c < n_c; c += NT) {
+                    const int b = bins[c];
+                    if (b >= b0 && b <= b1) tile_ids[atomicAdd(&s_tile, 1)] = c;
+                }
+                __syncthreads();
+                score_list(tile_ids, s_tile, [&](int p, unsigned long long k) { f(k, tile_ids[p]); });
+                __syncthreads();
+            }
+        };
+        auto weight = [&](int c) { return l == 0 ? 1ull : (unsigned long long)sizes[c]; };
+        unsigned long long limit = l == 0 ? (unsigned long long)P - 1 : band.clamp ? ~0ull : tp - above;
         if (tid == 0) {
-            unsigned long long run = 0;
-            int d = 0;
-            while (run + hist[d] < s_need) run += hist[d++];
-            s_need -= run;
-            wtot[0] = (unsigned long long)d;
+            s_n = 0;
+            s_eq = 0;
         }
         __syncthreads();
-        ipre |= (unsigned)wtot[0] << shift;
+        Crossing x{};
+        if (held) {
+            for_each_bin(bins, n_c, [&](int c, int b) {
+                if (b >= b0 && b <= b1) s_id[atomicAdd(&s_n, 1)] = c;
+            });
+            __syncthreads();
+            score_list(s_id, s_n, [&](int p, unsigned long long k) { s_key[p] = k; });
+        } else {
+            const unsigned stop = l == 0 ? kGather - kBandProbe : kGather;
+            x = find_crossing(
+                [&](auto&& f) { for_band([&](unsigned long long k, int c) { f(k, weight(c)); }, [] {}); }, limit, stop,
+                hist, wtot);
+            if (l == 0 || x.lo != x.hi) {  // (else x.lo is the score m_i)
+                // list A: every entry up to the range, or, of more than `stop` equal scores, as many of
+                // the lowest ids as are left to select (up to the end of a tile); list B: the range
+                const bool many = x.n > stop;
+                bool equal = true;  // uniform: this tile's entries of the range are wanted
+                for_band(
+                    [&](unsigned long long k, int c) {
+                        if (k > x.hi || (l == 1 && k < x.lo) || (k >= x.lo && !equal)) return;
+                        const int p = atomicAdd(&s_n, 1);
+                        s_key[p] = k;
+                        s_id[p] = c;
+                        if (k >= x.lo) atomicAdd(&s_eq, 1);
+                    },
+                    [&] { equal = !many || (unsigned long long)s_eq + x.before <= limit; });
+                if (l == 1) limit -= x.before;
+            }
+        }
+        __syncthreads();
+        const int n = s_n;
+        if (n > 0)
+            x = find_crossing(
+                [&](auto&& f) {
+                    for (int p = tid; p < n; p += NT) f(s_key[p], weight(s_id[p]));
+                },
+                limit, 0, hist, wtot);
+        if (l == 1) {
+            if (tid == 0) {
+                const int64_t m = to_fixed(key_score(x.lo));
+                a.m_fixed[t] = m;
+                if (a.dbg_m) a.dbg_m[t] = m;
+            }
+            break;
+        }
+        // among equal scores at the end of the selection, the lowest ids
+        const unsigned long long kth = x.lo;
+        const Crossing y = find_crossing(
+            [&](auto&& f) {
+                for (int p = tid; p < n; p += NT)
+                    if (s_key[p] == kth) f((unsigned long long)s_id[p], 1);
+            },
+            limit - x.before, 0, hist, wtot);
+        for (int j = tid; j < P; j += NT) {  // (ranks of scores that are not numbers stay empty)
+            s_sel[j] = -1;
+            s_base[j] = 0;
+            cum[j] = 0;
+        }
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        for (int p = tid; p < n; p += NT) {
+            if (s_key[p] > kth || (s_key[p] == kth && (unsigned long long)s_id[p] > y.lo)) continue;
+            const int r = atomicAdd(&s_n, 1);  // P of them
+            sA[r] = key_score(s_key[p]);
+            idA[r] = s_id[p];
+        }
+        __syncthreads();
+        rank_all(sA, idA, P, [&](int p, int r) {
+            const int c = idA[p];
+            s_sel[r] = c;
+            s_base[r] = (int32_t)to_fixed(sA[p]);
+            cum[r] = sizes[c];
+        });
+        __syncthreads();
+        int32_t* base = a.base + (int64_t)t * P;
+        int64_t* seg_pref = a.seg_pref + (int64_t)t * (P + 1);
+        for (int j = tid; j < P; j += NT) {
+            sel[j] = s_sel[j];
+            if (s_sel[j] >= 0) atomicAdd(&a.ccount[s_sel[j]], 1);
+            base[j] = s_base[j];
+            if (a.dbg_sel) a.dbg_sel[(int64_t)t * P + j] = s_sel[j];
+        }
+        block_inclusive_scan(cum, P, wtot);
+        for (int j = tid; j <= P; j += NT) seg_pref[j] = j == 0 ? 0 : cum[j - 1];
         __syncthreads();
     }
-    for (int c = tid; c < n_c; c += NT) {
-        const double v = score(c);
-        const unsigned long long k = key_of(v);
-        if (k < kth || (k == kth && (unsigned)c <= ipre)) {
-            const int p = atomicAdd(&s_n, 1);  // P of them
-            sA[p] = v;
-            idA[p] = c;
-        }
-        if (k == s_wpre) {  // every such centroid has the score m_i
-            a.m_fixed[t] = to_fixed(v);
-            if (a.dbg_m) a.dbg_m[t] = to_fixed(v);
-        }
-    }
-    int32_t* base = a.base + (int64_t)t * P;
-    int64_t* seg_pref = a.seg_pref + (int64_t)t * (P + 1);
-    __shared__ int s_sel[kSelCap], s_base[kSelCap];
-    for (int j = tid; j < P; j += NT) {  // (ranks of scores that are not numbers stay empty)
-        s_sel[j] = -1;
-        s_base[j] = 0;
-        cum[j] = 0;
-    }
-    __syncthreads();
-    rank_all(sA, idA, P, [&](int p, int r) {
-        const int c = idA[p];
-        s_sel[r] = c;
-        s_base[r] = (int32_t)to_fixed(sA[p]);
-        cum[r] = a.sizes[c];
-    });
-    __syncthreads();
-    for (int j = tid; j < P; j += NT) {
-        sel[j] = s_sel[j];
-        if (s_sel[j] >= 0) atomicAdd(&a.ccount[s_sel[j]], 1);
-        base[j] = s_base[j];
-        if (a.dbg_sel) a.dbg_sel[(int64_t)t * P + j] = s_sel[j];
-    }
-    block_inclusive_scan(cum, P, wtot);
-    for (int j = tid; j <= P; j += NT) seg_pref[j] = j == 0 ? 0 : cum[j - 1];
 }
 
 void launch_select_rest(const WaveArgs& a, hipStream_t s) {

@@ -179,6 +179,31 @@ def test_wide_selection_of_equal_centroids(t_prime):
         np.testing.assert_array_equal(fixed.cpu().numpy(), want["fixed"])
 
 
+@pytest.mark.parametrize("case", [
+    # n_centroids, coinciding centroids, their spread, nprobe, t'. A band of the selection holds more than
+    # 1,024 centroids: of normally spread scores around a t' in the middle (2.3% of the centroids:
+    # 1,600 and, more than the 10,240 that fit LDS, 11,700), or of coinciding and nearly coinciding ones
+    # on both sides of the 10,240, at the top and at the bottom of the order
+    (70001, 0, 0.0, 300, 0.5), (500000, 0, 0.0, 257, 0.5), (12000, 10240, 0.0, 300, 0.0), (12000, 10241, 0.0, 512, 0.0),
+    (16003, 15000, 0.0, 300, 0.4), (16003, 15000, 1e-4, 400, 0.4), (16003, 15000, 1e-4, 512, 0.0)])
+def test_wide_selection_of_large_bands(case):
+    import dataclasses
+
+    n_c, same, spread, nprobe, part = case
+    wl = synth.random_small_workload(31, n_centroids=n_c, n_docs=3000, max_len=24, nbits=4, n_queries=3, n_qtok=3,
+                                     nprobe=nprobe, t_prime=0, k=20)
+    data = synth.make_index(wl, workers=1)
+    if same:
+        rng = np.random.default_rng(7)
+        C, Q = data.centroids.copy(), data.queries.copy()
+        where = rng.permutation(n_c)[:same]
+        C[where] = C[0] + spread * rng.standard_normal((same, 128)).astype(np.float32)
+        C[where] /= np.linalg.norm(C[where].astype(np.float64), axis=1, keepdims=True).astype(np.float32)
+        Q[0, 0], Q[1, 1] = C[where[0]], -C[where[0]]
+        data = dataclasses.replace(data, centroids=C, queries=Q)
+    run_both(data, t_prime=int(part * data.n_embeddings), label=f"large bands {case}")
+
+
 def test_selection_band_overflow_falls_back_to_sorting():
     """2,000 identical centroids and a query token equal to them: all 2,000 share the top
     selection bin, more than the 1,024 that the band rescoring holds. The blocking search runs
