@@ -313,121 +313,152 @@ __global__ __launch_bounds__(256) void k_assign_near(const int32_t* __restrict__
     }
 }
 
-constexpr int kAllThreads = 1024;
-constexpr int kAllList = 4096;  // centroids in the band listed at once
+// S64 of two rows of 128 values, in dimension order (each product is exact).
+__device__ __forceinline__ double row_dot64(const float* __restrict__ a, const float* __restrict__ b) {
+    double v = 0.0;
+#pragma unroll 8
+    for (int d = 0; d < kDim / 4; ++d) {
+        const float4 p = reinterpret_cast<const float4*>(a)[d], q = reinterpret_cast<const float4*>(b)[d];
+        v = __builtin_fma((double)p.x, (double)q.x, v);
+        v = __builtin_fma((double)p.y, (double)q.y, v);
+        v = __builtin_fma((double)p.z, (double)q.z, v);
+        v = __builtin_fma((double)p.w, (double)q.w, v);
+    }
+    return v;
+}
 
-// The tokens whose blocks do not hold the whole band (all[0] of them), a workgroup each: every
-// centroid by its fp16 row (16 lanes each), those within the band in fp32 and, within 2^-15 of the
-// best, in fp64.
-__global__ __launch_bounds__(kAllThreads) void k_assign_all(const int32_t* __restrict__ all, const float* __restrict__ x,
+constexpr int kAllThreads = 1024;
+constexpr int kAllTokens = 16;   // tokens of a workgroup: the columns of one product, and a wave each
+constexpr int kAllList = 2048;   // centroids in the band listed per token
+
+// The tokens whose blocks do not hold the whole band (all[0] of them: centroids that coincide or
+// nearly so), kAllTokens to a workgroup: its waves stream the centroids' fp16 rows through the matrix
+// cores once for all of them and list, per token, the centroids within the band of the best filter
+// score (which the streams hold); each wave then scores one token's list in fp64. A token whose list
+// overflows is scored against every centroid. Bound by the rows, 4 MB per workgroup at 2^14
+// centroids, which 16 tokens share, and by the lists' fp32 rows.
+// Whole builds of a million tokens, 2^14 centroids and one k-means step (a workgroup per token that
+// reads the fp16 rows twice -> this; a score matrix for all tokens): 64 equal centroids near 1% of the
+// tokens 12.7 -> 7.8 ms (76.7), 900 near 5% 49 -> 12.5 ms (79); 900 near each of 300k tokens 257 -> 36 ms
+// (41); without equal centroids 7.0 ms (76.5).
+__global__ __launch_bounds__(kAllThreads) void k_assign_all(const int32_t* __restrict__ all,
+                                                            const AsStream* __restrict__ streams, int32_t splits,
+                                                            const float* __restrict__ x,
                                                             const _Float16* __restrict__ ch,
                                                             const float* __restrict__ cen, int32_t n_c,
                                                             int32_t* __restrict__ assign, int32_t* err) {
     constexpr int NW = kAllThreads / 64;
-    constexpr int U = 4;  // rows in flight per lane group
-    __shared__ __attribute__((aligned(16))) float s_x[kDim];
-    __shared__ float s_top[NW];
+    constexpr int U = 4;  // tiles of 16 centroids in flight per wave
+    static_assert(NW == kAllTokens, "a wave per token");
+    __shared__ int s_list[kAllTokens][kAllList];
+    __shared__ int s_n[kAllTokens];
+    __shared__ float s_thr[kAllTokens];
     __shared__ double s_best[NW];
-    __shared__ int s_id[NW], s_n, s_near;
-    __shared__ int s_list[kAllList];
+    __shared__ int s_id[NW], s_close;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, g = lane >> 4;
     const int n = all[0];
-    auto block_max = [&](float v) {  // ends with a barrier before the next use of s_top
-        for (int off = 32; off > 0; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off, 64));
-        if (lane == 0) s_top[wave] = v;
+    const int tiles = (n_c + 15) / 16;
+    for (int k0 = (int)blockIdx.x * kAllTokens; k0 < n; k0 += (int)gridDim.x * kAllTokens) {  // uniform
+        const int m = n - k0 < kAllTokens ? n - k0 : kAllTokens;
         __syncthreads();
-        for (int w = 0; w < NW; ++w) v = __builtin_fmaxf(v, s_top[w]);
-        __syncthreads();
-        return v;
-    };
-    for (int k = blockIdx.x; k < n; k += gridDim.x) {  // uniform
-        const int64_t t = all[1 + k];
-        __syncthreads();
-        if (tid < kDim) s_x[tid] = x[t * kDim + tid];
-        if (tid == 0) {
-            s_n = 0;
-            s_near = 0;
+        if (wave < m) {
+            const AsBlocks b = as_blocks(streams, splits * kAsStreams, all[1 + k0 + wave], lane);
+            if (lane == 0) {
+                s_thr[wave] = b.thr;
+                s_n[wave] = 0;
+            }
         }
         __syncthreads();
-        half8 xh;  // chunk lane % 16 of the token
+        // token operands: K step s: the lane's 8 values of token li (columns past the last repeat it)
+        half8 a[4];
+        const float4* xr = reinterpret_cast<const float4*>(x + (int64_t)all[1 + k0 + (li < m ? li : m - 1)] * kDim);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) xh[i] = (_Float16)s_x[8 * (lane & 15) + i];
-        // f(c, fp16 score of centroid c) on the 16 lanes of each centroid's group
-        auto for_scores = [&](auto&& f) {
-            for (int c0 = 4 * wave + (lane >> 4); c0 < n_c; c0 += U * 4 * NW) {
-                half8 w[U];
+        for (int s = 0; s < 4; ++s) {
+            const float4 u = xr[8 * s + 2 * g], v = xr[8 * s + 2 * g + 1];
+            a[s] = (half8){(_Float16)u.x, (_Float16)u.y, (_Float16)u.z, (_Float16)u.w,
+                           (_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
+        }
+        const float thr = li < m ? s_thr[li] : INFINITY;
+        for (int t0 = wave; t0 < tiles; t0 += U * NW) {  // wave-uniform
+            half8 c[U][4];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int c = c0 + u * 4 * NW;
-                    w[u] = *reinterpret_cast<const half8*>(ch + (int64_t)(c < n_c ? c : 0) * kDim + 8 * (lane & 15));
+            for (int u = 0; u < U; ++u) {  // (rows past n_c are there, up to a tile of 128)
+                const int t = t0 + u * NW < tiles ? t0 + u * NW : t0;
+                const half8* row = reinterpret_cast<const half8*>(ch + ((int64_t)t * 16 + li) * kDim);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) c[u][s] = row[4 * s + g];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(c[u][s], a[s], acc, 0, 0, 0);
+                // lane (li, g): centroids 16 t + 4 g + r against token li
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int cc = (t0 + u * NW) * 16 + 4 * g + r;
+                    if (acc[r] >= thr && cc < n_c) {
+                        const int p = atomicAdd(&s_n[li], 1);
+                        if (p < kAllList) s_list[li][p] = cc;
+                    }
                 }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    float v = 0.f;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        v = __builtin_amdgcn_fdot2((half2v){w[u][2 * i], w[u][2 * i + 1]}, (half2v){xh[2 * i], xh[2 * i + 1]}, v,
-                                                   false);
-                    for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
-                    const int c = c0 + u * 4 * NW;
-                    if (c < n_c) f(c, v);
-                }
             }
-        };
-        auto score32 = [&](int c) {
-            const float4* row = reinterpret_cast<const float4*>(cen + (int64_t)c * kDim);
-            float v = 0.f;
-            for (int d = 0; d < kDim / 4; ++d) {
-                const float4 w = row[d], y = reinterpret_cast<const float4*>(s_x)[d];
-                v = __builtin_fmaf(w.x, y.x, v);
-                v = __builtin_fmaf(w.y, y.y, v);
-                v = __builtin_fmaf(w.z, y.z, v);
-                v = __builtin_fmaf(w.w, y.w, v);
-            }
-            return v;
-        };
-        float top = -INFINITY;
-        for_scores([&](int, float v) { top = __builtin_fmaxf(top, v); });
-        const float thr = block_max(top) - 2.1f * kAssignEps;
-        for_scores([&](int c, float v) {
-            if ((lane & 15) == 0 && v >= thr) {
-                const int p = atomicAdd(&s_n, 1);
-                if (p < kAllList) s_list[p] = c;
-            }
-        });
-        __syncthreads();
-        const bool listed = s_n <= kAllList;  // uniform; else every centroid again
-        const int m = listed ? s_n : n_c;
-        top = -INFINITY;
-        for (int i = tid; i < m; i += kAllThreads) top = __builtin_fmaxf(top, score32(listed ? s_list[i] : i));
-        top = block_max(top);
-        double best = -INFINITY;
-        int id = INT32_MAX, near = 0;
-        for (int i = tid; i < m; i += kAllThreads) {
-            const int c = listed ? s_list[i] : i;
-            const float f = score32(c);
-            near += f >= top - 2.5f * kFilterEps ? 1 : 0;
-            if (f < top - 1.0f / 32768.0f) continue;
-            const float* row = cen + (int64_t)c * kDim;
-            double v = 0.0;
-            for (int d = 0; d < kDim; ++d) v = __builtin_fma((double)row[d], (double)s_x[d], v);
-            keep_best(best, id, v, c);
-        }
-        if (near) atomicAdd(&s_near, near);
-        for (int off = 32; off > 0; off >>= 1) {
-            const double ob = __shfl_xor(best, off, 64);
-            const int oi = __shfl_xor(id, off, 64);
-            keep_best(best, id, ob, oi);
-        }
-        if (lane == 0) {
-            s_best[wave] = best;
-            s_id[wave] = id;
         }
         __syncthreads();
-        if (tid == 0) {
-            for (int w = 1; w < NW; ++w) keep_best(best, id, s_best[w], s_id[w]);
-            assign[t] = id;
-            if (s_near > kAsCand) atomicOr(err, kErrArgOverflow);
+        if (wave < m && s_n[wave] <= kAllList) {  // wave-uniform: the list in fp64, a lane each
+            const int t = __builtin_amdgcn_readfirstlane(all[1 + k0 + wave]);
+            const float* xt = x + (int64_t)t * kDim;
+            const int nl = s_n[wave];
+            double best = -INFINITY;
+            int id = INT32_MAX;
+            for (int i = lane; i < nl; i += 64) {
+                const int c = s_list[wave][i];
+                keep_best(best, id, row_dot64(cen + (int64_t)c * kDim, xt), c);
+            }
+            for (int off = 32; off > 0; off >>= 1) {
+                const double ob = __shfl_xor(best, off, 64);
+                const int oi = __shfl_xor(id, off, 64);
+                keep_best(best, id, ob, oi);
+            }
+            if (lane == 0) assign[t] = id;
+            if (nl > kAsCand) {  // uniform: too many close ones?
+                int close = 0;
+                for (int i = lane; i < nl; i += 64)
+                    close += row_dot64(cen + (int64_t)s_list[wave][i] * kDim, xt) >= best - 2.5 * kFilterEps ? 1 : 0;
+                for (int off = 32; off > 0; off >>= 1) close += __shfl_xor(close, off, 64);
+                if (lane == 0 && close > kAsCand) atomicOr(err, kErrArgOverflow);
+            }
+        }
+        for (int w = 0; w < m; ++w) {  // every centroid, a thread each
+            if (s_n[w] <= kAllList) continue;  // uniform
+            const int64_t t = __builtin_amdgcn_readfirstlane(all[1 + k0 + w]);
+            const float* xt = x + t * kDim;
+            double best = -INFINITY;
+            int id = INT32_MAX;
+            for (int c = tid; c < n_c; c += kAllThreads) keep_best(best, id, row_dot64(cen + (int64_t)c * kDim, xt), c);
+            for (int off = 32; off > 0; off >>= 1) {
+                const double ob = __shfl_xor(best, off, 64);
+                const int oi = __shfl_xor(id, off, 64);
+                keep_best(best, id, ob, oi);
+            }
+            if (lane == 0) {
+                s_best[wave] = best;
+                s_id[wave] = id;
+            }
+            if (tid == 0) s_close = 0;
+            __syncthreads();
+            for (int v = 0; v < NW; ++v) keep_best(best, id, s_best[v], s_id[v]);
+            int close = 0;
+            for (int c = tid; c < n_c; c += kAllThreads)
+                close += row_dot64(cen + (int64_t)c * kDim, xt) >= best - 2.5 * kFilterEps ? 1 : 0;
+            if (close) atomicAdd(&s_close, close);
+            __syncthreads();
+            if (tid == 0) {
+                assign[t] = id;
+                if (s_close > kAsCand) atomicOr(err, kErrArgOverflow);
+            }
+            __syncthreads();
         }
     }
 }
@@ -480,7 +511,8 @@ void launch_assign(const float* x, int64_t n, const float* cen, int32_t n_c, voi
         hipLaunchKernelGGL(k_assign_pick, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, streams, splits, m, x + a * kDim,
                            ch, n_c, out + a, near, all);
         hipLaunchKernelGGL(k_assign_near, dim3(1024), dim3(256), 0, s, near, streams, splits, x + a * kDim, cen, n_c, out + a);
-        hipLaunchKernelGGL(k_assign_all, dim3(256), dim3(kAllThreads), 0, s, all, x + a * kDim, ch, cen, n_c, out + a, err);
+        hipLaunchKernelGGL(k_assign_all, dim3(256), dim3(kAllThreads), 0, s, all, streams, splits, x + a * kDim, ch,
+                           cen, n_c, out + a, err);
     }
 }
 

@@ -92,6 +92,27 @@ def test_build_nearest_centroid_blocks(n_c):
     _build_both(X, docs, len(lens), C0, sample, 1, 2, 300, label=f"{n_c} centroids, a third of them equal")
 
 
+@pytest.mark.parametrize("same,spread", [(30, 0.0), (130, 1e-4), (700, 0.0), (2500, 3e-4), (4500, 6e-4)])
+def test_build_close_centroids(same, spread):
+    """Tokens with more centroids near their best than the product keeps tiles for, a number of them
+    that is no multiple of the 16 that share a workgroup: lists of coinciding and of close centroids
+    per token, and more than the 2,048 that a list holds."""
+    import paper_2501_17788_amd as w
+
+    data, X, docs, lens = _inputs(62, n_docs=400, max_len=30, n_c=64)
+    rng = np.random.default_rng(same)
+    n_c = same + 77
+    C = rng.standard_normal((n_c, 128)).astype(np.float32)
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    where = rng.permutation(n_c)[:same]
+    C[where] = C[where[0]] + spread * rng.standard_normal((same, 128)).astype(np.float32)
+    near = rng.permutation(len(X))[:777]
+    X = X.copy()
+    X[near] = C[where[0]] + 0.1 * rng.standard_normal((len(near), 128)).astype(np.float32)
+    X[near] /= np.linalg.norm(X[near], axis=1, keepdims=True)
+    _build_both(X, docs, len(lens), C, np.sort(near[:500]).astype(np.int64), 1, 4, 300, label=f"{same} centroids within {spread}")
+
+
 def test_build_refuses_too_many_equal_centroids():
     """Centroids equal to a token's best are accepted up to 1,024; more are WARP_ENOTSUP."""
     import torch
