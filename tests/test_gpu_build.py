@@ -92,6 +92,21 @@ def test_build_nearest_centroid_blocks(n_c):
     _build_both(X, docs, len(lens), C0, sample, 1, 2, 300, label=f"{n_c} centroids, a third of them equal")
 
 
+@pytest.mark.parametrize("extra", [1, 70001])
+def test_build_second_chunk_of_tokens(extra):
+    """Tokens are assigned 2^19 at a time: one split of the centroids in a whole chunk, several in a
+    smaller last one, with tokens of coinciding centroids in both."""
+    n, n_c = (1 << 19) + extra, 500
+    rng = np.random.default_rng(extra)
+    C = rng.standard_normal((n_c, 128), dtype=np.float32)
+    C[7::20] = C[7]
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    X = C[rng.integers(0, n_c, n)] + 0.1 * rng.standard_normal((n, 128), dtype=np.float32)
+    X /= np.linalg.norm(X, axis=1, keepdims=True)
+    docs = (np.arange(n) // 50).astype(np.int32)
+    _build_both(X, docs, int(docs[-1]) + 1, C, np.arange(0, n, 1000, dtype=np.int64), 1, 2, 1000, label="2^19 tokens and more")
+
+
 @pytest.mark.parametrize("same,spread", [(30, 0.0), (130, 1e-4), (700, 0.0), (2500, 3e-4), (4500, 6e-4)])
 def test_build_close_centroids(same, spread):
     """Tokens with more centroids near their best than the product keeps tiles for, a number of them

@@ -99,18 +99,22 @@ CASES = [
     (13, 40, 303, 12, 4, 3, 32, 9, 100, 30),     # a document count that is not a multiple of 4
 ]
 
-# n_probe above 256 (the selection sorts every (token, centroid) score) and k above 4096 (the
-# top-k sorts every document key): the same results as the boundary-band selection and the
-# LDS top-k give below those limits
+# n_probe above 256 (a token whose band overflows is selected on the device) and above 512 (the
+# selection sorts every (token, centroid) score), k above 4096 (the top-k lists no blocks) and above
+# 16,384 (it sorts every document key): the same results as below those limits
 LARGE_CASES = [
     # seed, n_centroids, n_docs, max_len, nbits, n_queries, n_qtok, nprobe, t_prime, k
     (20, 600, 3000, 20, 4, 3, 32, 600, 1500, 5000),    # all clusters, k above n_docs
     (21, 1000, 20000, 20, 2, 4, 8, 300, 4000, 6000),   # 300 of 1000 clusters
     (22, 400, 2000, 10, 4, 2, 16, 400, 10 ** 9, 50),   # t' above N: lowest score
-    (23, 300, 2000, 10, 8, 2, 32, 257, 0, 4097),       # t' = 0, one past each limit
+    (23, 300, 2000, 10, 8, 2, 32, 257, 0, 4097),       # t' = 0, one past the first limits
     (24, 700, 5000, 12, 1, 5, 32, 520, 700, 4096),     # large n_probe alone
     (25, 60, 9000, 12, 4, 3, 32, 9, 100, 8000),        # large k alone
     (26, 4000, 40000, 6, 4, 3, 1, 260, 100, 10000),    # fewer candidates than k, one token
+    (27, 520, 17000, 10, 8, 2, 32, 513, 0, 16385),     # t' = 0, one past the sorts' limits
+    (28, 1000, 20000, 20, 2, 4, 8, 700, 4000, 18000),  # 700 of 1000 clusters
+    (29, 60, 30000, 12, 4, 3, 32, 9, 100, 17000),      # sorted top-k alone
+    (30, 4000, 40000, 6, 4, 3, 1, 600, 100, 20000),    # fewer candidates than a k that is sorted, one token
 ]
 
 
@@ -152,10 +156,22 @@ def test_selection_and_topk_sizes(case):
     run_both(synth.make_index(wl, workers=1), label=f"sizes {case}")
 
 
+@pytest.mark.parametrize("k", [4096, 4097, 16384])
+@pytest.mark.parametrize("n_docs", [1 << 18, (1 << 18) + 1])
+def test_topk_around_the_document_limit(n_docs, k):
+    """k in 4,097 .. 16,384 is gathered in LDS up to 2^18 documents and sorted above (most of the
+    documents here have no embedding)."""
+    wl = synth.random_small_workload(27, n_centroids=200, n_docs=30000, max_len=6, nbits=4, n_queries=2, n_qtok=6,
+                                     nprobe=60, t_prime=100, k=k)
+    data = synth.make_index(wl, workers=1)
+    data.workload = synth.with_overrides(wl, n_docs=n_docs)
+    run_both(data, label=f"{n_docs} documents k={k}")
+
+
 @pytest.mark.parametrize("t_prime", [0, 500, 20000, 10 ** 8])
 def test_wide_selection_of_equal_centroids(t_prime):
     """nprobe above 256 with 2,001 identical centroids: tokens whose band of equal scores does not
-    fit are selected from all their scores (the lowest ids first), at the top and at the bottom of
+    fit are selected from the whole band (the lowest ids first), at the top and at the bottom of
     the order, by the asynchronous search too."""
     import dataclasses
 

@@ -93,8 +93,9 @@ def test_noalloc_matches_async_tiny(literal):
 
 
 def test_noalloc_matches_async_large_nprobe_and_k():
-    """n_probe above 256 and k above 4096 take the sort-based selection and top-k, whose
-    sort buffers then also live in the static array."""
+    """n_probe above 512 and k above 16,384 take the sort-based selection and top-k, whose
+    sort buffers then also live in the static array; up to there, and above 256 and 4,096, the
+    selection and the top-k in LDS do, whose bands and gather buffers are the largest."""
     from paper_2501_17788_amd import Index
 
     data = synth.make_index(synth.random_small_workload(21, n_centroids=1000, n_docs=20000, max_len=20, nbits=2,
@@ -103,6 +104,9 @@ def test_noalloc_matches_async_large_nprobe_and_k():
     with Index.from_synthetic(data) as ix:
         _both(ix, data.queries, 300, 4000, 6000, "large 4")
         _both(ix, data.queries[1:3, :5], 600, 900, 5000, "large 2x5")
+        _both(ix, data.queries, 513, 4000, 16500, "sorted 4")
+        _both(ix, data.queries[1:3, :5], 1000, 900, 16385, "sorted 2x5")
+        _both(ix, data.queries[:3, :7], 512, 2000, 16384, "largest unsorted 3x7")
 
 
 def test_noalloc_rejects_an_index_too_large_for_its_scratch():
