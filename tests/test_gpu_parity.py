@@ -739,3 +739,29 @@ def test_topk_ties_and_block_pruning(cap, monkeypatch):
     wl = synth.random_small_workload(8, n_centroids=300, n_docs=5000, max_len=30, nbits=4, n_queries=3,
                                      n_qtok=32, nprobe=256, t_prime=2000, k=4096)
     run_both(synth.make_index(wl, workers=1), label=f"seed 8 cap={cap}")
+
+
+@pytest.mark.parametrize("group", [1, 37, 700, 3000])
+def test_topk_ties_across_the_gather_buffer(group):
+    """The k-th key inside a group of equal scores that ends past the gather buffer (k = 4,096 of
+    9,000 documents, k = 16,384 of 40,000): the exact radix select cuts the group by document."""
+    from helpers import pack_msb_first
+
+    w = _engine()
+    rng = np.random.default_rng(group)
+    C = rng.standard_normal((2, 128))
+    C = (C / np.linalg.norm(C, axis=1, keepdims=True)).astype(np.float32)
+    Q = rng.standard_normal((2, 8, 128))
+    Q = (Q / np.linalg.norm(Q, axis=2, keepdims=True)).astype(np.float32)
+    for n_docs, ks in ((9000, (4096, 4090)), (40000, (16384, 16300))):
+        kinds = rng.integers(0, 4, (-(-n_docs // group), 128))
+        codes = pack_msb_first(kinds[np.arange(n_docs) // group], 2)
+        order = rng.permutation(n_docs)
+        arrays = dict(centroids=C, offsets=np.array([0, n_docs // 3, n_docs], np.int64),
+                      doc_ids=np.concatenate([np.sort(order[:n_docs // 3]), np.sort(order[n_docs // 3:])]).astype(np.int32),
+                      codes=codes, nbits=2, bucket_weights=np.array([-0.05, -0.01, 0.01, 0.05], np.float32), n_docs=n_docs)
+        for k in ks:
+            say(f"[ties of {group}] {n_docs} documents k={k}")
+            with w.Index(**arrays) as ix:
+                got = ix.search_debug(Q, 2, 0, k)
+            compare(got, oracle.search(queries=Q, nprobe=2, t_prime=0, k=k, **arrays), label=f"ties of {group} k={k}")
