@@ -12,15 +12,16 @@
 // its fp16 row again, it is the argmax; else the blocks are scored in fp32 (within 2^-17 of S64),
 // and if more than one centroid remains within 2^-15 of the best of these, in fp64. A token with
 // a third block in the band (centroids that coincide or nearly so) is scored against every
-// centroid by k_assign_all. So the result is the exact argmax for every input.
+// centroid again by k_assign_all, sixteen such tokens at a time. So the result is the exact argmax for every input.
 //
 // The product is bound by the matrix cores: a wave computes 64 tokens x 64 centroids with its
 // tokens' operands in registers; the centroids stream through two 32 KB LDS tiles that are
 // loaded straight from memory (16 bytes per lane, rows swizzled by their number so that the
 // operand reads meet no bank twice).
 // Measured (1M tokens, 2^14 centroids, with four k-means steps on 125k of them): the whole build
-// 96.3 -> 10.9 ms; the product 5.3 ms (1.19 PFLOP/s), the picks 2.1 + 1.1 + 0.4 ms, against 39 ms
-// for a split-fp16 product that wrote fp32 scores and 51 ms to read them.
+// 96.3 -> 11.0 ms, the same when calls repeat (10.4 ms of kernels; the scratch's allocation and release
+// 0.4 ms, the stream's 0.2 ms); the product 5.2 ms (1.19 PFLOP/s), the picks 2.1 + 1.1 + 0.4 ms, against
+// 39 ms for a split-fp16 product that wrote fp32 scores and 51 ms to read them.
 #include <algorithm>
 
 #include "engine.h"
@@ -472,7 +473,8 @@ static int32_t assign_splits(int64_t n, int32_t n_c) {
     return (int32_t)(s < 1 ? 1 : (s > 8 ? 8 : s));
 }
 
-// Tokens assigned at once: their streams take at most about 64 MB (and a split's, eight times that).
+// Tokens assigned at once: 160 bytes of streams each and split, 84 MB for a whole chunk (one split) and at
+// most about twice that (two splits, just below it).
 static int64_t assign_chunk(int64_t n) { return std::min<int64_t>(n, (int64_t)1 << 19); }
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }

@@ -13,9 +13,13 @@ constexpr int kFrac = 26;          // fixed-point fraction bits of token and doc
 constexpr int kMaxQtok = 32;       // query_maxlen
 constexpr int kMaxProbe = 256;     // largest n_probe whose selection reports a band overflow as an error
 constexpr int kBandProbe = 512;    // largest n_probe of the band selection (above kMaxProbe a token whose band
-                                   // overflows is selected from all its scores); above, the sorting one
+                                   // overflows is selected from its whole bands); above, the sorting one. List
+                                   // A holds the n_probe best and their last bins' others in kSelCap entries,
+                                   // and k_select_rest ranks one entry per thread. Whole searches, sorted / by
+                                   // bands, nprobe 512: one query 555 / 470 us at 600 centroids, 552 / 268 us
+                                   // at 2^15, 2.72 / 0.35 ms at 2^18; 128 queries 28.8 / 28.5, 42.6 / 2.5, 342 / 4.2 ms
 constexpr int kMaxK = 4096;        // largest k of the LDS top-k with a list of blocks
-constexpr int kMaxKLarge = 16384;  // largest k of the LDS top-k without one; above, every key is sorted
+constexpr int kMaxKLarge = 16384;  // largest k of the LDS top-k without one (128 KB of keys); above, every key is sorted
 constexpr int kMaxKDocs = 1 << 18; // most documents of the latter (one workgroup reads a query's keys three times)
 constexpr int kMaxDocs = 1 << 24;  // document ids packed into the low 24 bits of a sort key
 constexpr int kTopkListCap = 4096;  // blocks of 256 documents the top-k's pruned passes can list
@@ -46,7 +50,12 @@ __device__ __forceinline__ int score_bin(float f) {
 // embeddings, group of up to kMxGroup probing tokens), run by kMxBlock threads.
 constexpr int kMxChunk = 256;
 constexpr int kMxGroup = 32;
-constexpr int kMxGroupSmall = 16;   // in waves of at most kMxSmallTokens tokens (k_scan_small)
+// Waves of at most kMxSmallTokens tokens scan in one launch with groups of kMxGroupSmall (k_scan_small).
+// Whole searches, two launches and groups of 32 / one launch and groups of 16, at 130k (b = 4), 6.3M (b = 4)
+// and 70M embeddings (b = 2): 34 tokens 111 / 111, 183 / 178, 530 / 496 us; 64 tokens 116 / 112, 218 / 202,
+// 739 / 691 us; 128 tokens 117 / 115, 270 / 263, 1082 / 1110 us; 256 tokens 126 / 115, 332 / 339, 1675 / 1696 us;
+// one query of 32 tokens at k_scan_small. So the line could lie at 64; from 128 on larger collections lose.
+constexpr int kMxGroupSmall = 16;
 constexpr int kMxSmallTokens = 32;
 constexpr int kMxBlock = 256;
 // The persistent scan grid takes its items in batches of kScanBatch consecutive items:

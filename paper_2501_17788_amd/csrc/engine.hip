@@ -487,9 +487,18 @@ void clear_slots(warp_index* idx, hipStream_t s) {
 // above kBandProbe, and in the blocking search's retry after a band overflowed.
 bool full_select(const warp_index* idx, int32_t P) { return P > kBandProbe || idx->force_full_select; }
 
-// The top-k sorts every document key of a query for k above kMaxKLarge, and above kMaxK where one
-// workgroup would read too many keys (100k documents, k = 5,000, 8 queries: 2.30 ms of sorts, one
-// query after another, against 0.17 ms).
+// The top-k sorts every document key of a query, one query after another, for k above kMaxKLarge, and
+// above kMaxK where one workgroup would read too many keys. Whole searches, sorted / gathered in LDS:
+//   n_docs     k       1 query        8 queries       128 queries
+//   20,000     5,000   279 / 186 us   1.46 / 0.25 ms  21.7 / 1.24 ms
+//   20,000     16,384  278 / 283 us   1.46 / 0.36 ms  21.6 / 1.43 ms
+//   2^18       5,000   486 / 388 us   2.84 / 1.08 ms  45.9 / 14.9 ms
+//   2^18       16,384  486 / 526 us   2.86 / 1.72 ms  45.6 / 15.6 ms
+//   300,000    16,384  513 / 594 us   2.93 / 1.30 ms  48.0 / 17.6 ms
+//   1,000,000  5,000   943 / 1031 us  5.57 / 3.76 ms  91.5 / 57.0 ms
+//   1,000,000  16,384  942 / 1323 us  5.59 / 5.75 ms  91.4 / 57.3 ms
+// So the line at 2^18 documents gives away batches above it (up to 3x at 300,000), and one query with
+// the largest k just below it pays 8%; what a query alone loses grows with the documents.
 bool full_topk(const warp_index* idx, int32_t k) {
     return k > kMaxKLarge || (k > kMaxK && idx->n_docs > kMaxKDocs);
 }
@@ -891,8 +900,7 @@ int read_device_errors(warp_index* idx, hipStream_t s, int32_t* bits = nullptr) 
         return fail(WARP_EINVAL, "a query token is not finite or has norm > 1 + 1e-3");
     if (err & kErrSelOverflow)
         return fail(WARP_ENOTSUP,
-                    "centroid selection overflow: more than %d centroids fall in one selection band "
-                    "(degenerate centroid scores)", kSelCap);
+                    "centroid selection overflow: more than %d centroids fall in one selection band", kSelCap);
     if (err & kErrSelNoCrossing) return fail(WARP_EDEVICE, "centroid selection found no t' crossing");
     return WARP_OK;
 }
@@ -925,7 +933,7 @@ int search_host(warp_index* idx, const float* queries, int32_t n_queries, int32_
                 (int32_t*)idx->st_counts.p,  sel ? (int32_t*)idx->st_sel.p : nullptr,
                 m ? (int64_t*)idx->st_m.p : nullptr, bitmap ? (uint32_t*)idx->st_bitmap.p : nullptr,
                 scored ? (int64_t*)idx->st_scored.p : nullptr};
-    // A band of the selection that overflowed (a degenerate centroid set) is retried once with the
+    // A band of the selection that overflowed (P up to kMaxProbe) is retried once with the
     // selection that sorts every score, which has no band to overflow.
     int32_t bits = 0;
     for (int attempt = 0; attempt < 2; ++attempt) {

@@ -9,7 +9,7 @@
 // fp32). The split and the dropped lo x lo term change a score by at most
 // 3 * 2^-22 sum_d |q_d c_d| + 2^-24 sqrt(128), about 1.4e-6 for unit vectors, and the
 // fp32 accumulation of the 384 products by at most gamma_384 sum_d |q_d c_d| (2.3e-5):
-// within the 2^-13 that centroid selection and the index build assume. These scores
+// within the 2^-13 that centroid selection assumes. These scores
 // only steer selection: every centroid that lands near a selection boundary is
 // rescored in fp64, so no result depends on how they were accumulated.
 //
@@ -177,7 +177,8 @@ __global__ __launch_bounds__(256, 2) void k_filter_gemm(const float* __restrict_
 // flight while it multiplies: bound by the one read of the centroids. Four waves of a workgroup
 // take adjacent centroids, so that their 32-byte pieces of a row of bins meet in L2.
 // One query of 32 tokens, whole search, with this kernel instead of the tiled one: 1,024 centroids
-// 85.0 -> 81.3 us, 2^15 158 -> 153 us.
+// 85.0 -> 81.3 us, 2^15 158 -> 153 us. (32 tokens, the most of one query, are what the operands hold in 171
+// VGPRs; more of them, in up to the 256 that two workgroups leave each other, have not been measured.)
 constexpr int kFewTokens = 32;
 __global__ __launch_bounds__(256, 2) void k_filter_few(const float* __restrict__ q, int32_t n_tok,
                                                        const float* __restrict__ cen, int32_t n_c,

@@ -3,7 +3,8 @@
 // takes), and each probed cluster is cut into work items of (kMxChunk embeddings) x
 // (mx_group tokens), so that the residual scan reads a cluster chunk once for all the
 // tokens that probe it. Pair order inside a bucket follows atomic arrival and does not
-// affect results: the token-level max is exact and commutative. Three launches: block
+// affect results: the token-level max is exact and commutative. Three launches (two up to
+// 2^16 chunks and 2^19 clusters, whose emit blocks sum the block totals themselves): block
 // sums of the counts (with the pair offsets inside each block of clusters), their
 // prefixes, then the buckets and the lists of probed chunks.
 #include "engine.h"

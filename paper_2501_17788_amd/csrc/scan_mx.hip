@@ -118,8 +118,8 @@ __device__ __forceinline__ void weight_tables(const float* weights, unsigned (&t
 
 // Selector of a nibble's half of its table, bytes 4 .. 7 (of the upper eight entries) where bit 2 of
 // the byte is set, else 0 .. 3. The mask sits in a vector register, so that this is one v_and_or_b32.
-// (101 instead of 108 VALU instructions per b = 4 tile: 256 queries at 6.3M embeddings 4.41 -> 4.35 ms, one
-// query 154.5 -> 152.8 us, 64 queries at 240M 60.4 -> 59.9 ms.)
+// (101 instead of 108 VALU instructions per b = 4 tile. One query at 6.3M embeddings 152.2 -> 150.8 us, 1% in
+// each of three comparisons whose runs differ by 0.3%; batches 0 .. 1%, within what their runs differ.)
 __device__ __forceinline__ unsigned nibble_pick(unsigned x) {
     unsigned mask = 0x04040404u;
     asm("" : "+v"(mask));
@@ -1027,8 +1027,8 @@ __global__ __launch_bounds__(kMxBlock) void k_scan_narrow(WaveArgs a) {
 // Waves of at most kMxSmallTokens tokens: both scans in one launch. Every workgroup first takes
 // its share of the narrow scan's chunks, then items of the wide scan from the batch counter, so
 // the workgroups that end their chunks early take more of the items, and there is one ramp and
-// one tail instead of two. Token groups of 16 (26 KB of LDS, and at b <= 2 127 VGPRs) put four
-// workgroups on a CU instead of three; a cluster that few tokens probe loses nothing by the
+// one tail instead of two. Token groups of 16 (29 KB of LDS, the narrow scan's part of the union, and at
+// b <= 2 125 VGPRs) put four workgroups on a CU instead of three; a cluster that few tokens probe loses nothing by the
 // smaller groups, whereas in larger waves each group's repeated decode costs more.
 // One query of 32 tokens, two launches -> one: 1,024 clusters 87 -> 85 us, 6.3M embeddings (b = 4)
 // 181 -> 158 us, 70M (b = 2) 490 -> 452 us, 600M (b = 2) 3.13 -> 2.94 ms for the whole search. Groups of

@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WaveArgs a) {
     int32_t* base = a.base + (int64_t)t * P;
     int64_t* seg_pref = a.seg_pref + (int64_t)t * (P + 1);
     if (nA > kSelCap || nB > kSelCap || nA < P || nB < 1) {
-        // degenerate score distribution: leave a token that probes and scans nothing
+        // a band too large for its list: leave a token that probes and scans nothing
         for (int j = tid; j < P; j += NT) {
             sel[j] = -1;
             base[j] = 0;
