@@ -19,7 +19,8 @@ constexpr int kBandProbe = 512;    // largest n_probe of the band selection (abo
                                    // bands, nprobe 512: one query 555 / 470 us at 600 centroids, 552 / 268 us
                                    // at 2^15, 2.72 / 0.35 ms at 2^18; 128 queries 28.8 / 28.5, 42.6 / 2.5, 342 / 4.2 ms
 constexpr int kMaxK = 4096;        // largest k of the LDS top-k with a list of blocks
-constexpr int kMaxKLarge = 16384;  // largest k of the LDS top-k without one (128 KB of keys); above, every key is sorted
+constexpr int kMaxKLarge = 16384;  // largest k of the LDS top-k without one (128 KB of keys); above, and for
+                                   // some k above 8,000 of one query (full_topk), every key is sorted
 constexpr int kMaxKDocs = 1 << 18; // most documents of the latter (one workgroup reads a query's keys three times)
 constexpr int kMaxDocs = 1 << 24;  // document ids packed into the low 24 bits of a sort key
 constexpr int kTopkListCap = 4096;  // blocks of 256 documents the top-k's pruned passes can list

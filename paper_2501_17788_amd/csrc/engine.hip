@@ -497,10 +497,18 @@ bool full_select(const warp_index* idx, int32_t P) { return P > kBandProbe || id
 //   300,000    16,384  513 / 594 us   2.93 / 1.30 ms  48.0 / 17.6 ms
 //   1,000,000  5,000   943 / 1031 us  5.57 / 3.76 ms  91.5 / 57.0 ms
 //   1,000,000  16,384  942 / 1323 us  5.59 / 5.75 ms  91.4 / 57.3 ms
-// So the line at 2^18 documents gives away batches above it (up to 3x at 300,000), and one query with
-// the largest k just below it pays 8%; what a query alone loses grows with the documents.
-bool full_topk(const warp_index* idx, int32_t k) {
-    return k > kMaxKLarge || (k > kMaxK && idx->n_docs > kMaxKDocs);
+// So the line at 2^18 documents gives away batches above it (up to 3x at 300,000).
+// One query alone is one workgroup in LDS against a sort on the whole chip. Above 8,000 keys the
+// workgroup sorts 16,384 of them, and near the end of its buffer it needs another pass over the keys:
+//   n_docs     k = 5,000 .. 8,000   8,192 / 12,000 .. 14,000         16,384
+//   20,000     279 / 186 us         231 / 236 us (k = 12,288)        230 / 248 us
+//   65,536                          259 / 253, 261 / 261 us          259 / 278 us
+//   131,072                         326 / 297, 326 / 301 us          324 / 330 us
+//   200,000    348 / 262 us         348 / 342, 347 / 346 us
+//   2^18       370 / 325 us         370 / 379, 372 / 390 us          372 / 435 us
+bool full_topk(const warp_index* idx, int32_t k, int32_t n_q) {
+    if (k > kMaxKLarge || (k > kMaxK && idx->n_docs > kMaxKDocs)) return true;
+    return n_q == 1 && k > 8000 && (k > 14336 || idx->n_docs < (1 << 16) || idx->n_docs > 200000);
 }
 
 // Workgroups per token of the selection for a wave of n_tok tokens: one for large waves; for
@@ -526,9 +534,9 @@ int64_t split_tokens(const warp_index* idx, int64_t n_tok) {
     return select_slices(idx, n_tok) > 1 ? n_tok : 0;
 }
 
-// Device scratch for a wave of `qw` queries of `T` tokens; the fills are enqueued on the
+// Device scratch for waves of `qw` queries of `T` tokens and a last one of `last`; the fills are enqueued on the
 // search stream `s`, after the searches before it.
-int reserve(warp_index* idx, int32_t qw, int32_t T, int32_t P, int32_t k, hipStream_t s) {
+int reserve(warp_index* idx, int32_t qw, int32_t last, int32_t T, int32_t P, int32_t k, hipStream_t s) {
     const int64_t n_tok = (int64_t)qw * T;
     int rc = WARP_OK;
     if (!rc) rc = grow_scratch(idx, idx->filter, (size_t)n_tok * idx->n_c * 2);
@@ -551,7 +559,7 @@ int reserve(warp_index* idx, int32_t qw, int32_t T, int32_t P, int32_t k, hipStr
     if (!rc) rc = grow_scratch(idx, idx->cblk, (size_t)cblocks * 24);
     if (!rc) rc = grow_scratch(idx, idx->scan_queue, 256);
     if (!rc && full_select(idx, P)) rc = grow_scratch(idx, idx->full_sel, select_full_bytes(n_tok, idx->n_c));
-    if (!rc && full_topk(idx, k)) rc = grow_scratch(idx, idx->full_topk, topk_full_bytes(idx->n_docs));
+    if (!rc && (full_topk(idx, k, qw) || full_topk(idx, k, last))) rc = grow_scratch(idx, idx->full_topk, topk_full_bytes(idx->n_docs));
     const int64_t st = split_tokens(idx, n_tok);
     if (!rc) rc = grow_scratch(idx, idx->sel_hist, (size_t)st * kSelBins * 8);
     if (!rc) rc = grow_scratch(idx, idx->sel_lists, (size_t)st * 2 * kSelCap * 4);
@@ -857,7 +865,7 @@ hipError_t launch_wave(warp_index* idx, const WaveScratch& w, const float* dq, i
     mark(4);
     launch_fold(a, s);
     mark(5);
-    if (full_topk(idx, k)) {
+    if (full_topk(idx, k, nq) && w.full_topk) {
         const hipError_t e = launch_topk_full(a, w.full_topk, s);
         if (err == hipSuccess) err = e;
     } else {
@@ -876,7 +884,7 @@ int enqueue_search(warp_index* idx, const float* dq, int32_t n_queries, int32_t 
     if ((P > kMaxProbe || idx->force_full_select) && (int64_t)T * idx->n_c > ((int64_t)1 << 31))
         return fail(WARP_ENOTSUP, "the sorted selection needs n_qtok * n_centroids <= 2^31");
     const int32_t qw = wave_queries(idx, n_queries, T, P);
-    int rc = reserve(idx, qw, T, P, k, s);
+    int rc = reserve(idx, qw, (n_queries - 1) % qw + 1, T, P, k, s);
     if (rc) return rc;
     const WaveScratch w = index_scratch(idx);
     for (int32_t q0 = 0; q0 < n_queries; q0 += qw) {
@@ -993,7 +1001,8 @@ size_t noalloc_layout(const warp_index* idx, int32_t qw, int32_t T, int32_t P, i
     w.tokcnt = literal ? (uint32_t*)take(n_tok * nd * 4) : nullptr;
     w.q_epoch = nullptr;  // cells hold t + 2^31 and the fold resets every cell it reads
     w.full_sel = P > kBandProbe ? take(select_full_bytes((int64_t)n_tok, idx->n_c)) : nullptr;
-    w.full_topk = full_topk(idx, k) ? take(topk_full_bytes(idx->n_docs)) : nullptr;
+    // (a single query's sort is only the faster way: what the waves leave, in warp_search_noalloc)
+    w.full_topk = full_topk(idx, k, 2) ? take(topk_full_bytes(idx->n_docs)) : nullptr;
     w.split_cap = split_tokens(idx, (int64_t)n_tok);
     w.sel_hist = (unsigned long long*)take((size_t)w.split_cap * kSelBins * 8);
     w.sel_lists = (int32_t*)take((size_t)w.split_cap * 2 * kSelCap * 4);
@@ -1034,7 +1043,9 @@ int warp_search_noalloc(warp_index* idx, const float* queries, int32_t n_queries
     }
     const int32_t qw = lo;
     WaveScratch w{};
-    noalloc_layout(idx, qw, n_qtok, nprobe, k, literal, base, &w);
+    const size_t used = noalloc_layout(idx, qw, n_qtok, nprobe, k, literal, base, &w);
+    if (!w.full_topk && full_topk(idx, k, 1) && used + topk_full_bytes(idx->n_docs) <= kNoAllocBytes)
+        w.full_topk = base + used;
     hipStream_t s = (hipStream_t)hip_stream;
     // the array keeps what the last call left: the token-max cells (and counts) start at
     // zero; each wave's fold then resets every cell it reads

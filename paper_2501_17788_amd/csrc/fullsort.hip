@@ -1,6 +1,6 @@
 // Exact paths for requests beyond what the selection and top-k kernels hold in LDS
 // (n_probe above kBandProbe; k above kMaxKLarge or, with more than kMaxKDocs documents,
-// above kMaxK; and, up to n_probe kMaxProbe, a selection band of more than kSelCap
+// above kMaxK, or one query above 8,000 (full_topk); and, up to n_probe kMaxProbe, a selection band of more than kSelCap
 // centroids in the blocking search's retry): whole score lists are sorted with the device
 // radix sort, which gives the definitions of Sections 4.3 and 4.5 directly.
 //

@@ -168,6 +168,33 @@ def test_topk_around_the_document_limit(n_docs, k):
     run_both(data, label=f"{n_docs} documents k={k}")
 
 
+@pytest.mark.parametrize("n_docs", [(1 << 16) - 1, 1 << 16, 200000, 200001])
+def test_topk_of_one_query(n_docs, monkeypatch):
+    """Above k = 8,000 a wave of one query sorts every key for some k and numbers of documents where
+    larger waves do not: a call of one query, the last wave of a call of five, and the static array."""
+    import torch
+
+    w = _engine()
+    wl = synth.random_small_workload(28, n_centroids=100, n_docs=30000, max_len=4, nbits=2, n_queries=5, n_qtok=3,
+                                     nprobe=100, t_prime=100, k=100)
+    data = synth.make_index(wl, workers=1)
+    data.workload = synth.with_overrides(wl, n_docs=n_docs)
+    for k in (8000, 8001, 14336, 14337):
+        want = oracle.search_index(data, k=k)
+        with w.Index.from_synthetic(data) as ix:
+            # about 20 bytes per document and query: waves of two, two and one
+            monkeypatch.setenv("WARP_SCRATCH_MB", str((45 * n_docs >> 20) + 1))
+            say(f"[top-k of one query] {n_docs} documents k={k}")
+            compare(ix.search_debug(data.queries, 100, 100, k), want, label=f"{n_docs} documents k={k}, five queries")
+            monkeypatch.delenv("WARP_SCRATCH_MB")
+            one = {key: v[4:] for key, v in want.items() if isinstance(v, np.ndarray)}
+            compare(ix.search_debug(data.queries[4:], 100, 100, k), one, label=f"{n_docs} documents k={k}, one query")
+            ids, scores, counts, fixed = ix.search_noalloc(torch.from_numpy(data.queries[4:]).cuda(), 100, 100, k)
+            ix.sync()
+            for got, key in ((ids, "ids"), (scores, "scores"), (counts, "counts"), (fixed, "fixed")):
+                np.testing.assert_array_equal(got.cpu().numpy(), one[key], err_msg=f"noalloc k={k}: {key}")
+
+
 @pytest.mark.parametrize("t_prime", [0, 500, 20000, 10 ** 8])
 def test_wide_selection_of_equal_centroids(t_prime):
     """nprobe above 256 with 2,001 identical centroids: tokens whose band of equal scores does not
