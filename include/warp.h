@@ -168,8 +168,9 @@ int warp_index_info(const warp_index* idx, int32_t* n_centroids, int64_t* n_embe
  *                Above 256, WARP_ENOTSUP if n_qtok * n_centroids > 2^31
  *   t_prime      >= 0, in embeddings
  *   k            >= 1. Up to 4096 (up to 16384 if n_docs <= 2^18) the top-k
- *                gathers the best keys in LDS; above, it sorts every document
- *                key of a query (same results)
+ *                gathers the best keys in LDS; above, and for one query with
+ *                some k above 8000, it sorts every document key of a query
+ *                (same results)
  *   out_doc_ids  [n_queries][k] caller-owned host; -1 past the result count
  *   out_scores   [n_queries][k] caller-owned host; -inf past the result count
  *   out_counts   [n_queries] host or NULL: min(k, number of candidate documents)

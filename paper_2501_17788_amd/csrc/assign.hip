@@ -12,16 +12,18 @@
 // its fp16 row again, it is the argmax; else the blocks are scored in fp32 (within 2^-17 of S64),
 // and if more than one centroid remains within 2^-15 of the best of these, in fp64. A token with
 // a third block in the band (centroids that coincide or nearly so) is scored against every
-// centroid again by k_assign_all, sixteen such tokens at a time. So the result is the exact argmax for every input.
+// centroid again by k_assign_all, sixteen such tokens at a time. So the result is the exact argmax
+// for every input.
 //
 // The product is bound by the matrix cores: a wave computes 64 tokens x 64 centroids with its
 // tokens' operands in registers; the centroids stream through two 32 KB LDS tiles that are
 // loaded straight from memory (16 bytes per lane, rows swizzled by their number so that the
 // operand reads meet no bank twice).
 // Measured (1M tokens, 2^14 centroids, with four k-means steps on 125k of them): the whole build
-// 96.3 -> 11.0 ms, the same when calls repeat (10.4 ms of kernels; the scratch's allocation and release
-// 0.4 ms, the stream's 0.2 ms); the product 5.2 ms (1.19 PFLOP/s), the picks 2.1 + 1.1 + 0.4 ms, against
-// 39 ms for a split-fp16 product that wrote fp32 scores and 51 ms to read them.
+// 96.3 -> 11.0 ms (10.4 ms of kernels; the scratch's allocation and release 0.4 ms, the stream's 0.2 ms);
+// the product 5.2 ms (1.19 PFLOP/s), the picks 2.1 + 1.1 + 0.4 ms, against 39 ms for a split-fp16 product
+// that wrote fp32 scores and 51 ms to read them. In a process that has freed tens of GB before (large
+// indexes), hipMalloc has to reclaim memory: it takes 4 to 12 ms instead of 0.1 and the call 15 to 23 ms.
 #include <algorithm>
 
 #include "engine.h"
