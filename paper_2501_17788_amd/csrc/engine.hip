@@ -534,9 +534,9 @@ int64_t split_tokens(const warp_index* idx, int64_t n_tok) {
     return select_slices(idx, n_tok) > 1 ? n_tok : 0;
 }
 
-// Device scratch for waves of `qw` queries of `T` tokens and a last one of `last`; the fills are enqueued on the
+// Device scratch for a wave of `qw` queries of `T` tokens; the fills are enqueued on the
 // search stream `s`, after the searches before it.
-int reserve(warp_index* idx, int32_t qw, int32_t last, int32_t T, int32_t P, int32_t k, hipStream_t s) {
+int reserve(warp_index* idx, int32_t qw, int32_t T, int32_t P, int32_t k, hipStream_t s) {
     const int64_t n_tok = (int64_t)qw * T;
     int rc = WARP_OK;
     if (!rc) rc = grow_scratch(idx, idx->filter, (size_t)n_tok * idx->n_c * 2);
@@ -559,7 +559,7 @@ int reserve(warp_index* idx, int32_t qw, int32_t last, int32_t T, int32_t P, int
     if (!rc) rc = grow_scratch(idx, idx->cblk, (size_t)cblocks * 24);
     if (!rc) rc = grow_scratch(idx, idx->scan_queue, 256);
     if (!rc && full_select(idx, P)) rc = grow_scratch(idx, idx->full_sel, select_full_bytes(n_tok, idx->n_c));
-    if (!rc && (full_topk(idx, k, qw) || full_topk(idx, k, last))) rc = grow_scratch(idx, idx->full_topk, topk_full_bytes(idx->n_docs));
+    if (!rc && full_topk(idx, k, 2)) rc = grow_scratch(idx, idx->full_topk, topk_full_bytes(idx->n_docs));
     const int64_t st = split_tokens(idx, n_tok);
     if (!rc) rc = grow_scratch(idx, idx->sel_hist, (size_t)st * kSelBins * 8);
     if (!rc) rc = grow_scratch(idx, idx->sel_lists, (size_t)st * 2 * kSelCap * 4);
@@ -884,8 +884,11 @@ int enqueue_search(warp_index* idx, const float* dq, int32_t n_queries, int32_t 
     if ((P > kMaxProbe || idx->force_full_select) && (int64_t)T * idx->n_c > ((int64_t)1 << 31))
         return fail(WARP_ENOTSUP, "the sorted selection needs n_qtok * n_centroids <= 2^31");
     const int32_t qw = wave_queries(idx, n_queries, T, P);
-    int rc = reserve(idx, qw, (n_queries - 1) % qw + 1, T, P, k, s);
+    int rc = reserve(idx, qw, T, P, k, s);
     if (rc) return rc;
+    // (a single query's sort is only the faster way: without room for its scratch, the top-k in LDS)
+    if ((n_queries - 1) % qw == 0 && full_topk(idx, k, 1))
+        (void)grow_scratch(idx, idx->full_topk, topk_full_bytes(idx->n_docs));
     const WaveScratch w = index_scratch(idx);
     for (int32_t q0 = 0; q0 < n_queries; q0 += qw) {
         const int32_t nq = n_queries - q0 < qw ? n_queries - q0 : qw;
@@ -1001,7 +1004,6 @@ size_t noalloc_layout(const warp_index* idx, int32_t qw, int32_t T, int32_t P, i
     w.tokcnt = literal ? (uint32_t*)take(n_tok * nd * 4) : nullptr;
     w.q_epoch = nullptr;  // cells hold t + 2^31 and the fold resets every cell it reads
     w.full_sel = P > kBandProbe ? take(select_full_bytes((int64_t)n_tok, idx->n_c)) : nullptr;
-    // (a single query's sort is only the faster way: what the waves leave, in warp_search_noalloc)
     w.full_topk = full_topk(idx, k, 2) ? take(topk_full_bytes(idx->n_docs)) : nullptr;
     w.split_cap = split_tokens(idx, (int64_t)n_tok);
     w.sel_hist = (unsigned long long*)take((size_t)w.split_cap * kSelBins * 8);
@@ -1044,6 +1046,7 @@ int warp_search_noalloc(warp_index* idx, const float* queries, int32_t n_queries
     const int32_t qw = lo;
     WaveScratch w{};
     const size_t used = noalloc_layout(idx, qw, n_qtok, nprobe, k, literal, base, &w);
+    // (as in enqueue_search: in what the waves leave)
     if (!w.full_topk && full_topk(idx, k, 1) && used + topk_full_bytes(idx->n_docs) <= kNoAllocBytes)
         w.full_topk = base + used;
     hipStream_t s = (hipStream_t)hip_stream;

@@ -171,7 +171,8 @@ def test_topk_around_the_document_limit(n_docs, k):
 @pytest.mark.parametrize("n_docs", [(1 << 16) - 1, 1 << 16, 200000, 200001])
 def test_topk_of_one_query(n_docs, monkeypatch):
     """Above k = 8,000 a wave of one query sorts every key for some k and numbers of documents where
-    larger waves do not: a call of one query, the last wave of a call of five, and the static array."""
+    larger waves do not: a call of one query, also without room for the sort, the last wave of a call of
+    five, and the static array."""
     import torch
 
     w = _engine()
@@ -181,13 +182,18 @@ def test_topk_of_one_query(n_docs, monkeypatch):
     data.workload = synth.with_overrides(wl, n_docs=n_docs)
     for k in (8000, 8001, 14336, 14337):
         want = oracle.search_index(data, k=k)
+        one = {key: v[4:] for key, v in want.items() if isinstance(v, np.ndarray)}
+        with w.Index.from_synthetic(data) as ix:
+            ix.search_debug(data.queries[3:], 100, 100, k)  # (two queries: no sort)
+            monkeypatch.setenv("WARP_MAX_SCRATCH_BYTES", "1")  # no room for the sort's scratch any more
+            compare(ix.search_debug(data.queries[4:], 100, 100, k), one, label=f"{n_docs} documents k={k}, no scratch")
+            monkeypatch.delenv("WARP_MAX_SCRATCH_BYTES")
         with w.Index.from_synthetic(data) as ix:
             # about 20 bytes per document and query: waves of two, two and one
             monkeypatch.setenv("WARP_SCRATCH_MB", str((45 * n_docs >> 20) + 1))
             say(f"[top-k of one query] {n_docs} documents k={k}")
             compare(ix.search_debug(data.queries, 100, 100, k), want, label=f"{n_docs} documents k={k}, five queries")
             monkeypatch.delenv("WARP_SCRATCH_MB")
-            one = {key: v[4:] for key, v in want.items() if isinstance(v, np.ndarray)}
             compare(ix.search_debug(data.queries[4:], 100, 100, k), one, label=f"{n_docs} documents k={k}, one query")
             ids, scores, counts, fixed = ix.search_noalloc(torch.from_numpy(data.queries[4:]).cuda(), 100, 100, k)
             ix.sync()
