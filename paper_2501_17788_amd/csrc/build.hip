@@ -61,14 +61,14 @@ __global__ void k_kmeans_normalize(const unsigned long long* __restrict__ sums,
 
 // rows of 128 fp32 values scaled to unit norm: (float)(x_d / ||x||), the norm in fp64 (sum
 // of squares in dimension order, IEEE sqrt); the rows were checked to be finite and nonzero
-__global__ void k_normalize_rows(float* __restrict__ rows, int32_t n) {
+__global__ void k_normalize_rows(const float* __restrict__ rows, int32_t n, float* __restrict__ out) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n) return;
-    float* r = rows + (int64_t)c * kDim;
+    const float* r = rows + (int64_t)c * kDim;
     double ss = 0.0;
     for (int d = 0; d < kDim; ++d) ss += (double)r[d] * (double)r[d];
     const double norm = __builtin_sqrt(ss);
-    for (int d = 0; d < kDim; ++d) r[d] = (float)((double)r[d] / norm);
+    for (int d = 0; d < kDim; ++d) out[(int64_t)c * kDim + d] = (float)((double)r[d] / norm);
 }
 
 // residual components of tokens [0, n): x - C[assign]
@@ -145,11 +145,20 @@ __global__ __launch_bounds__(256) void k_encode(const float* __restrict__ x, con
     if (word == 0) doc_ids[p] = token_docs[t];
 }
 
-// First starting vector that is not finite or whose squared norm is zero or not finite, one
-// thread each: *first becomes the smallest 2 c + (finite).
-__global__ void k_check_start(const float* __restrict__ rows, int32_t n, unsigned long long* first) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n) return;
+// Blocks [0, cb): the first starting vector that is not finite or whose squared norm is zero or not
+// finite, one thread each: *first becomes the largest ~(2 c + (finite)). Blocks [cb, ...): the first
+// sample id outside [0, n_tokens), first[1] the largest ~i.
+constexpr int kCheckBlock = 64;
+__global__ __launch_bounds__(kCheckBlock) void k_check_build(const float* __restrict__ rows, int32_t n_c, int32_t cb,
+                                                             const int64_t* __restrict__ ids, int64_t n, int64_t n_tokens,
+                                                             unsigned long long* first) {
+    if ((int)blockIdx.x >= cb) {
+        const int64_t i = (int64_t)((int)blockIdx.x - cb) * kCheckBlock + threadIdx.x;
+        if (i < n && (ids[i] < 0 || ids[i] >= n_tokens)) atomicMax(first + 1, ~(unsigned long long)i);
+        return;
+    }
+    const int c = blockIdx.x * kCheckBlock + threadIdx.x;
+    if (c >= n_c) return;
     const float4* r = reinterpret_cast<const float4*>(rows + (int64_t)c * kDim);
     double ss = 0.0;
     bool finite = true;
@@ -161,13 +170,7 @@ __global__ void k_check_start(const float* __restrict__ rows, int32_t n, unsigne
         ss += (double)v.z * v.z;
         ss += (double)v.w * v.w;
     }
-    if (!finite || !(ss > 0.0) || !__builtin_isfinite(ss)) atomicMin(first, 2ull * (unsigned)c + (finite ? 1 : 0));
-}
-
-// First sample id outside [0, n_tokens).
-__global__ void k_check_sample(const int64_t* __restrict__ ids, int64_t n, int64_t n_tokens, unsigned long long* first) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && (ids[i] < 0 || ids[i] >= n_tokens)) atomicMin(first, (unsigned long long)i);
+    if (!finite || !(ss > 0.0) || !__builtin_isfinite(ss)) atomicMax(first, ~(2ull * (unsigned)c + (finite ? 1 : 0)));
 }
 
 __global__ void k_count_clusters(const int32_t* __restrict__ assign, int64_t n, unsigned long long* counts) {
@@ -200,8 +203,8 @@ void launch_kmeans_normalize(const unsigned long long* sums, const unsigned long
     hipLaunchKernelGGL(k_kmeans_normalize, dim3(blocks_for(n_c, 64)), dim3(64), 0, s, sums, counts, n_c, cen);
 }
 
-void launch_normalize_rows(float* rows, int32_t n, hipStream_t s) {
-    if (n > 0) hipLaunchKernelGGL(k_normalize_rows, dim3(blocks_for(n, 64)), dim3(64), 0, s, rows, n);
+void launch_normalize_rows(const float* rows, int32_t n, float* out, hipStream_t s) {
+    if (n > 0) hipLaunchKernelGGL(k_normalize_rows, dim3(blocks_for(n, 64)), dim3(64), 0, s, rows, n, out);
 }
 
 void launch_residuals(const float* x, const int32_t* assign, int64_t n, const float* cen, float* out,
@@ -231,8 +234,9 @@ void launch_encode(int32_t nbits, const float* x, const int32_t* token_docs, con
 
 void launch_check_build(const float* rows, int32_t n_c, const int64_t* ids, int64_t n, int64_t n_tokens,
                         unsigned long long* first, hipStream_t s) {
-    hipLaunchKernelGGL(k_check_start, dim3(blocks_for(n_c, 64)), dim3(64), 0, s, rows, n_c, first);
-    hipLaunchKernelGGL(k_check_sample, dim3(blocks_for(n, 256)), dim3(256), 0, s, ids, n, n_tokens, first + 1);
+    const unsigned cb = blocks_for(n_c, kCheckBlock);
+    hipLaunchKernelGGL(k_check_build, dim3(cb + blocks_for(n, kCheckBlock)), dim3(kCheckBlock), 0, s, rows, n_c, (int32_t)cb,
+                       ids, n, n_tokens, first);
 }
 
 void launch_count_clusters(const int32_t* assign, int64_t n, unsigned long long* counts, hipStream_t s) {

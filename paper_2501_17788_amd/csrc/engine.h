@@ -210,7 +210,7 @@ void launch_kmeans_accum(const float* xs, const int32_t* assign, int64_t n, unsi
                          unsigned long long* counts, hipStream_t s);
 void launch_kmeans_normalize(const unsigned long long* sums, const unsigned long long* counts, int32_t n_c,
                              float* cen, hipStream_t s);
-void launch_normalize_rows(float* rows, int32_t n, hipStream_t s);
+void launch_normalize_rows(const float* rows, int32_t n, float* out, hipStream_t s);
 void launch_residuals(const float* x, const int32_t* assign, int64_t n, const float* cen, float* out,
                       hipStream_t s);
 void launch_pick_quantiles(const float* sorted, int64_t n, int32_t nbits, float* cutoffs, float* weights,
@@ -218,8 +218,8 @@ void launch_pick_quantiles(const float* sorted, int64_t n, int32_t nbits, float*
 void launch_encode(int32_t nbits, const float* x, const int32_t* token_docs, const int32_t* assign,
                    const int64_t* perm, int64_t n, const float* cen, const float* cutoffs, uint8_t* codes,
                    int32_t* doc_ids, hipStream_t s);
-// first[0]: the smallest 2 c + (whether it is finite) of an unusable starting vector c; first[1]: the
-// first sample id out of range (both untouched where there is none)
+// first[0]: ~(2 c + (whether it is finite)) of the first unusable starting vector c; first[1]: ~i of the
+// first sample id i out of range (both, zero before, untouched where there is none)
 void launch_check_build(const float* rows, int32_t n_c, const int64_t* ids, int64_t n, int64_t n_tokens,
                         unsigned long long* first, hipStream_t s);
 void launch_count_clusters(const int32_t* assign, int64_t n, unsigned long long* counts, hipStream_t s);

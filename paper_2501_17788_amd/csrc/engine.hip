@@ -1221,8 +1221,8 @@ int warp_build_index(const float* tokens, const int32_t* token_docs, int64_t n_t
         exclusive_sum_u64(nullptr, &t3, nullptr, nullptr, n_c + 1, s) != hipSuccess)
         return done(fail(WARP_EDEVICE, "device primitive sizing failed"));
     struct {
-        int32_t *err, *assign, *assign_s, *keys;
-        unsigned long long *first, *sums, *counts;
+        int32_t *assign, *assign_s, *keys;
+        unsigned long long *flags, *sums;
         void *match, *temp;
         float *xs, *resid, *sorted;
         int64_t *perm_in, *perm;
@@ -1235,15 +1235,13 @@ int warp_build_index(const float* tokens, const int32_t* token_docs, int64_t n_t
             if (mem.p) *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>((char*)mem.p + at);
             at += (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255;
         };
-        take(&w.err, 4);
-        take(&w.first, 16);
+        take(&w.flags, 24);
         take(&w.assign, assignment ? 0 : (size_t)N * 4);
         take((char**)&w.match,
              std::max(assign_scratch_bytes(N, n_centroids), assign_scratch_bytes(n_sample, n_centroids)));
         take(&w.xs, (size_t)n_sample * kDim * 4);
         take(&w.assign_s, (size_t)n_sample * 4);
-        take(&w.sums, (size_t)n_c * kDim * 8);
-        take(&w.counts, ((size_t)n_c + 1) * 8);
+        take(&w.sums, ((size_t)n_c * kDim + n_c + 1) * 8);  // and the counts
         take(&w.resid, (size_t)n_quant * kDim * 4);
         take(&w.sorted, (size_t)n_quant * kDim * 4);
         take(&w.perm_in, (size_t)N * 8);
@@ -1256,7 +1254,7 @@ int warp_build_index(const float* tokens, const int32_t* token_docs, int64_t n_t
             if (rc) return done(rc);
         }
     }
-    int32_t* err = w.err;
+    int32_t* err = (int32_t*)(w.flags + 2);
     int32_t* assign = assignment ? assignment : w.assign;
 
     // inputs: usable starting vectors, sample ids in range, finite tokens of norm <= 1 + 1e-3,
@@ -1265,46 +1263,39 @@ int warp_build_index(const float* tokens, const int32_t* token_docs, int64_t n_t
     auto try_hip = [&](hipError_t e, const char* what) {
         return e == hipSuccess ? WARP_OK : fail(WARP_EDEVICE, "%s failed: %s", what, hipGetErrorString(e));
     };
-    launch_fill_i32(err, 1, 0, s);
-    launch_fill_i32((int32_t*)w.first, 4, -1, s);
+    launch_fill_i32((int32_t*)w.flags, 6, 0, s);
     float* start = (float*)w.sums;
     rc = try_hip(hipMemcpyAsync(start, init_centroids, (size_t)n_c * kDim * 4, hipMemcpyDefault, s),
                  "copying the starting vectors");
     if (rc) return done(rc);
-    launch_check_build(start, n_centroids, sample_ids, n_sample, N, w.first, s);
+    launch_check_build(start, n_centroids, sample_ids, n_sample, N, w.flags, s);
     launch_check_queries(tokens, N, err, s);
     launch_check_docs(token_docs, N, n_docs, err, s);
-    int32_t herr = 0;
-    unsigned long long first[2];
-    rc = try_hip(hipMemcpyAsync(&herr, err, 4, hipMemcpyDeviceToHost, s), "reading the checks");
-    if (!rc) rc = try_hip(hipMemcpyAsync(first, w.first, 16, hipMemcpyDeviceToHost, s), "reading the checks");
+    unsigned long long flags[3];  // the two of launch_check_build, the error bits
+    rc = try_hip(hipMemcpyAsync(flags, w.flags, 24, hipMemcpyDeviceToHost, s), "reading the checks");
     if (!rc) rc = try_hip(hipStreamSynchronize(s), "checking the inputs");
     if (rc) return done(rc);
-    if (first[0] != ~0ull) {
-        const long long c = (long long)(first[0] >> 1);
-        return done((first[0] & 1) ? fail(WARP_EINVAL, "starting vector %lld is zero or too large", c)
+    int32_t herr = (int32_t)flags[2];
+    if (flags[0]) {
+        const long long c = (long long)(~flags[0] >> 1);
+        return done((~flags[0] & 1) ? fail(WARP_EINVAL, "starting vector %lld is zero or too large", c)
                                    : fail(WARP_EINVAL, "starting vector %lld is not finite", c));
     }
-    if (first[1] != ~0ull)
-        return done(fail(WARP_EINVAL, "sample id %lld is out of range", (long long)first[1]));
+    if (flags[1]) return done(fail(WARP_EINVAL, "sample id %lld is out of range", (long long)~flags[1]));
     if (herr & kErrQueryNorm) return done(fail(WARP_EINVAL, "a token is not finite or has norm > 1 + 1e-3"));
     if (herr & kErrDocRange) return done(fail(WARP_EINVAL, "a token's document id is outside [0, n_docs)"));
 
-    rc = try_hip(hipMemcpyAsync(centroids, start, (size_t)n_c * kDim * 4, hipMemcpyDeviceToDevice, s),
-                 "copying the starting vectors");
-    if (rc) return done(rc);
-    launch_normalize_rows(centroids, n_centroids, s);  // the starting centroids
+    launch_normalize_rows(start, n_centroids, centroids, s);  // the starting centroids
     auto assign_rows = [&](const float* x, int64_t n, int32_t* out) {
         launch_assign(x, n, centroids, n_centroids, w.match, out, err, s);
     };
     // k-means on the sample
     float* xs = w.xs;
     launch_gather_rows(tokens, sample_ids, n_sample, xs, s);
-    auto *sums = w.sums, *counts = w.counts;
+    auto *sums = w.sums, *counts = w.sums + n_c * kDim;
     for (int it = 0; it < iterations; ++it) {
         assign_rows(xs, n_sample, w.assign_s);
-        launch_fill_i32((int32_t*)sums, n_c * kDim * 2, 0, s);
-        launch_fill_i32((int32_t*)counts, (n_c + 1) * 2, 0, s);
+        launch_fill_i32((int32_t*)sums, (n_c * kDim + n_c + 1) * 2, 0, s);
         launch_kmeans_accum(xs, w.assign_s, n_sample, sums, counts, s);
         launch_kmeans_normalize(sums, counts, n_centroids, centroids, s);
     }

@@ -77,11 +77,12 @@ def test_build_edge_cases():
     got, _ = _build_both(X, docs, len(lens), C1, sample, 2, 4, 200, label="duplicate centroids")
 
 
-@pytest.mark.parametrize("n_c", [1, 127, 129, 640])
+@pytest.mark.parametrize("n_c", [1, 127, 129, 256, 257, 640])
 def test_build_nearest_centroid_blocks(n_c):
     """The nearest-centroid search works on tiles of 128 centroids and keeps two tiles per lane:
     centroid counts around a tile's edge, and sets in which every third centroid coincides, so that
-    more tiles tie than a lane keeps (every centroid is then scored; ties go to the lowest id)."""
+    more tiles tie than a lane keeps (every centroid is then scored; ties go to the lowest id), which
+    up to two tiles cannot."""
     import paper_2501_17788_amd as w
 
     data, X, docs, lens = _inputs(60, n_docs=500, max_len=40, n_c=64)
@@ -176,6 +177,30 @@ def test_build_errors():
     assert e.value.code == w.EINVAL and "document id" in e.value.msg
     with pytest.raises(w.WarpError):
         w.build_index(Xt, Dt, len(lens), C0, sample, 1, 3, 10)
+
+
+def test_build_names_the_first_refused_input():
+    import torch
+
+    import paper_2501_17788_amd as w
+
+    data, X, docs, lens = _inputs(41, n_docs=200, max_len=12, n_c=200)
+    sample = w.sample_passages(lens, c=20.0, seed=1)
+    C0 = w.initial_centroids(X, sample, 200, seed=2)
+    Xt, Dt = torch.from_numpy(X).cuda(), torch.from_numpy(docs).cuda()
+    for first, second, what in ((0, np.nan, "vector 5 is zero"), (np.inf, 0, "vector 5 is not finite"),
+                                (np.nan, np.nan, "vector 5 is not finite")):
+        Z = C0.copy()
+        Z[5, :], Z[150, 3], Z[199, :] = first, second, 0
+        with pytest.raises(w.WarpError) as e:
+            w.build_index(Xt, Dt, len(lens), Z, sample, 1, 4, 10)
+        assert e.value.code == w.EINVAL and what in e.value.msg
+    for at in (0, 70, len(sample) - 1):
+        bad = sample.copy()
+        bad[at:] = -1 if at == 70 else len(X)
+        with pytest.raises(w.WarpError) as e:
+            w.build_index(Xt, Dt, len(lens), C0, bad, 1, 4, 10)
+        assert e.value.code == w.EINVAL and f"sample id {at} " in e.value.msg
 
 
 def test_build_starts_after_the_null_stream():
