@@ -20,7 +20,7 @@
 // loaded straight from memory (16 bytes per lane, rows swizzled by their number so that the
 // operand reads meet no bank twice).
 // Measured (1M tokens, 2^14 centroids, with four k-means steps on 125k of them): the whole build
-// 96.3 -> 11.0 ms (10.4 ms of kernels; the scratch's allocation and release 0.4 ms, the stream's 0.2 ms);
+// 96.3 -> 11.0 ms (10.3 ms of kernels; the scratch's allocation and release 0.4 ms, the stream's 0.2 ms);
 // the product 5.2 ms (1.19 PFLOP/s), the picks 2.1 + 1.1 + 0.4 ms, against 39 ms for a split-fp16 product
 // that wrote fp32 scores and 51 ms to read them. In a process that has freed tens of GB before (large
 // indexes), hipMalloc has to reclaim memory: it takes 4 to 12 ms instead of 0.1 and the call 15 to 23 ms.

@@ -497,7 +497,7 @@ bool full_select(const warp_index* idx, int32_t P) { return P > kBandProbe || id
 //   300,000    16,384  513 / 594 us   2.93 / 1.30 ms  48.0 / 17.6 ms
 //   1,000,000  5,000   943 / 1031 us  5.57 / 3.76 ms  91.5 / 57.0 ms
 //   1,000,000  16,384  942 / 1323 us  5.59 / 5.75 ms  91.4 / 57.3 ms
-// So the line at 2^18 documents gives away batches above it (up to 3x at 300,000).
+// So the line at 2^18 documents gives away batches above it (up to 2.7x at 300,000).
 // One query alone is one workgroup in LDS against a sort on the whole chip. Above 8,000 keys the
 // workgroup sorts 16,384 of them, and near the end of its buffer it needs another pass over the keys:
 //   n_docs     k = 5,000 .. 8,000   8,192 / 12,000 .. 14,000         16,384

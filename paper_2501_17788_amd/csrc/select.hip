@@ -594,8 +594,8 @@ constexpr int kRestTile = 4096;  // centroids looked at together where a band ho
 
 // Selection of the tokens that k_select left (sel[0] = -2: a band of more than kSelCap centroids),
 // for P <= kSelThreads: one workgroup per token (the others' exit at once) over the same two bands,
-// which need not be small here: the five bins around the t' crossing hold 4% of the centroids where
-// t' lies in the middle of normally spread scores, 5,200 of 2^17. A band of at most kRestCap
+// which need not be small here: the five bins around the t' crossing hold 2.3% of the centroids where
+// t' lies in the middle of normally spread scores, 3,000 of 2^17. A band of at most kRestCap
 // centroids is scored once, into LDS; a larger one (half a million centroids, or many that
 // coincide) is scored again in each of the few rounds that narrow it to what fits. The P first
 // are ranked as in k_select.
